@@ -627,27 +627,24 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
     HIP_TRY(hipEventCreate(&S.ev2));
     HIP_TRY(hipEventCreate(&S.ev3));
 
-    // ---- validate on the device
+    // ---- validate on the device (its parts fit where the summary's partial sums go later)
     HIP_TRY(hipMemsetAsync(S.ctl, 0, CTL_BYTES, s));
+    static_assert(sizeof(ValPart) * VAL_BLOCKS_MAX <= sizeof(double) * 256 * 6, "validation parts");
+    ValPart* vpart = reinterpret_cast<ValPart*>(S.sumblk);
     HIP_TRY(launch_validate(p->n, p->d, p->layout, p->x, p->ldx, p->layout == SVM_DENSE_FEATURE_MAJOR, p->row_ptr,
-                            p->col, p->val, p->y, S.ctl, s));
-    int rc = S.read_ctl();
-    if (rc) return rc;
-    if (S.h.err & 1) return SVM_EINVAL;
-    if (S.h.err & 2) return SVM_ENONFINITE;
-    if (S.h.n_pos == 0 || S.h.n_neg == 0) return SVM_EONECLASS;
+                            p->col, p->val, p->y, vpart, s));
+    ValPart vhost[VAL_BLOCKS_MAX];
+    HIP_TRY(hipMemcpyAsync(vhost, vpart, sizeof(ValPart) * val_blocks(p->n), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    const ValPart v = val_sum(vhost, p->n);
+    if (v.flags & VAL_MALFORMED) return SVM_EINVAL;
+    if (v.flags & VAL_NONFINITE) return SVM_ENONFINITE;
+    if (v.n_pos == 0 || v.n_neg == 0) return SVM_EONECLASS;
+    int rc = SVM_OK;
 
     if (p->layout == SVM_CSR) {
-        S.max_row_nnz = S.h.max_row_nnz;
-        int32_t nnz = 0;
-        HIP_TRY(hipMemcpyAsync(&nnz, p->row_ptr + p->n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(launch_check_pattern(0, nullptr, S.counts + 2, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        HIP_TRY(launch_check_pattern(nnz, p->val, S.counts + 2, s));
-        int32_t notpat = 1;
-        HIP_TRY(hipMemcpyAsync(&notpat, S.counts + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        S.pattern_only = notpat == 0;
+        S.max_row_nnz = v.max_row_nnz;
+        S.pattern_only = !(v.flags & VAL_NOT_ONES);
         S.lay = p->d <= TABLE_MAX_D ? LAY_CSR_TABLE : LAY_CSR_SLOT;
         if (S.lay == LAY_CSR_SLOT && S.max_row_nnz > SLOT_MAX_NNZ) return SVM_EUNSUPPORTED;
         S.lpr = q->lanes_per_row ? q->lanes_per_row : 1;   // refined with the LDS plan below
@@ -1157,21 +1154,22 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     int32_t* bc = (int32_t*)(ws + P.bc);
     int32_t* ct = (int32_t*)(ws + P.ct);
     double* pt = (double*)(ws + P.pt);
-    // both sample sets are validated first (labels, CSR structure, finite values)
-    Ctl* ctl = (Ctl*)(ws + P.ctl);
-    HIP_TRY(hipMemsetAsync(ctl, 0, 2 * CTL_BYTES, s));
+    // both sample sets are validated first (labels, CSR structure, finite values); the parts go
+    // where the coefficients (8 B a row) and the partial sums (128 B a query) go later
+    ValPart* vt = (ValPart*)cf;
+    ValPart* vq = (ValPart*)pt;
     HIP_TRY(launch_validate(n, d, train->layout, train->x, train->ldx, train->layout == SVM_DENSE_FEATURE_MAJOR,
-                            train->row_ptr, train->col, train->val, train->y, ctl, s));
-    Ctl* ctlq = (Ctl*)(ws + P.ctl + CTL_BYTES);
+                            train->row_ptr, train->col, train->val, train->y, vt, s));
     HIP_TRY(launch_validate(nq, d, queries->layout, queries->x, queries->ldx,
                             queries->layout == SVM_DENSE_FEATURE_MAJOR, queries->row_ptr, queries->col, queries->val,
-                            nullptr, ctlq, s));
-    Ctl hv[2];
-    HIP_TRY(hipMemcpyAsync(&hv[0], ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&hv[1], ctlq, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+                            nullptr, vq, s));
+    ValPart hvt[VAL_BLOCKS_MAX], hvq[VAL_BLOCKS_MAX];
+    HIP_TRY(hipMemcpyAsync(hvt, vt, sizeof(ValPart) * val_blocks(n), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(hvq, vq, sizeof(ValPart) * val_blocks(nq), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if ((hv[0].err | hv[1].err) & 1) return SVM_EINVAL;
-    if ((hv[0].err | hv[1].err) & 2) return SVM_ENONFINITE;
+    const ValPart valt = val_sum(hvt, n), valq = val_sum(hvq, nq);
+    if ((valt.flags | valq.flags) & VAL_MALFORMED) return SVM_EINVAL;
+    if ((valt.flags | valq.flags) & VAL_NONFINITE) return SVM_ENONFINITE;
     if (dense) {
         HIP_TRY(launch_pack_dense(n, d, dpad, train->x, train->ldx, train->layout == SVM_DENSE_FEATURE_MAJOR, xt, s));
         HIP_TRY(launch_pack_dense(nq, d, dpad, queries->x, queries->ldx, queries->layout == SVM_DENSE_FEATURE_MAJOR,
@@ -1195,11 +1193,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     int blocks = 0;
     if (!dense && d <= BITS_MAX_D) {
         // binary rows on both sides: bitsets and popcounts (exact squared distances)
-        bool tp = false, qp = false;
-        int rc = csr_pattern_only(train, ct + 2, s, &tp);
-        if (rc) return rc;
-        if (tp && (rc = csr_pattern_only(queries, ct + 3, s, &qp))) return rc;
-        if (tp && qp) {
+        if (!((valt.flags | valq.flags) & VAL_NOT_ONES)) {
             a.lay = LAY_BITS;
             a.wpr = bits_wpr(d);
             a.abits = (uint32_t*)(ws + P.qbits);
@@ -1268,7 +1262,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
         } else if (R < 1) {
             // wide CSR queries: slot-map densification of groups of query rows (longest row from
             // the validation pass)
-            const int mx = hv[1].max_row_nnz;
+            const int mx = valq.max_row_nnz;
             if (mx > SLOT_MAX_NNZ) return SVM_EUNSUPPORTED;
             a.lay = LAY_CSR_SLOT;
             a.rows_per_block = mx;

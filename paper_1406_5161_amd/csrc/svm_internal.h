@@ -44,10 +44,6 @@ struct Ctl {
     int64_t shrunk_total;
     int32_t exit_reason;
     int32_t abort;
-    int32_t err;              // validation error bits
-    int32_t n_pos, n_neg;
-    int32_t max_row_nnz;
-    int32_t pad0;
     int64_t cache_both;       // iterations whose two kernel rows both came from the row cache
 };
 static_assert(sizeof(Ctl) <= 256, "Ctl must fit in its slot");
@@ -170,9 +166,28 @@ struct SumArgs {
 int slot_rows_for(int d, int max_nnz);
 
 // ---- launch wrappers (device code in svm_kernels.hip)
+// What one workgroup of the input validation found in its rows; the host adds them up.
+enum : int { VAL_MALFORMED = 1, VAL_NONFINITE = 2, VAL_NOT_ONES = 4 };   // the last: a CSR value other than 1.0
+struct ValPart {
+    int32_t flags, n_pos, n_neg, max_row_nnz, nnz;
+};
+constexpr int VAL_BLOCKS_MAX = 256;
+// workgroups of the validation of n rows (a part each); their parts take at most n / 2 + 20 bytes
+inline int val_blocks(int n) { return n >= 64 * VAL_BLOCKS_MAX ? VAL_BLOCKS_MAX : (n + 63) / 64; }
 hipError_t launch_validate(int n, int d, int lay, const float* x, int64_t ldx, int feature_major,
-                           const int32_t* rp, const int32_t* col, const float* val, const int8_t* y, Ctl* ctl,
+                           const int32_t* rp, const int32_t* col, const float* val, const int8_t* y, ValPart* part,
                            hipStream_t s);
+inline ValPart val_sum(const ValPart* part, int n) {
+    ValPart t{};
+    for (int b = 0; b < val_blocks(n); ++b) {
+        t.flags |= part[b].flags;
+        t.n_pos += part[b].n_pos;
+        t.n_neg += part[b].n_neg;
+        if (part[b].max_row_nnz > t.max_row_nnz) t.max_row_nnz = part[b].max_row_nnz;
+        t.nnz = part[b].nnz;
+    }
+    return t;
+}
 hipError_t launch_pack_dense(int n, int d, int dpad, const float* x, int64_t ldx, int feature_major, float* out,
                              hipStream_t s);
 hipError_t launch_init_state(int n, const int8_t* y, double C, int warm, double* alpha, double* f, uint8_t* status,

@@ -158,32 +158,34 @@ int64_t shrink_h(const svm_params_t* q, int n) {
     return (int64_t)std::max(1.0, h);
 }
 
-// Validate on the device and learn the CSR nonzero count and whether every value is 1.0.
-int inspect(const svm_problem_t* p, Ctl* vctl, hipStream_t s, Inspect* out) {
-    hipError_t e = hipMemsetAsync(vctl, 0, sizeof(Ctl), s);
-    if (e == hipSuccess)
+// Validate k problems on the device, with one wait for all of them, and learn each CSR nonzero
+// count and whether every value is 1.0.  The first problem that fails gives the error.
+int inspect(int k, const svm_problem_t* probs, hipStream_t s, Inspect* out) {
+    ValPart* part = nullptr;
+    const size_t bytes = sizeof(ValPart) * VAL_BLOCKS_MAX * (size_t)k;
+    if (hipMalloc(&part, bytes) != hipSuccess) return SVM_ENOMEM;
+    hipError_t e = hipSuccess;
+    for (int j = 0; j < k && e == hipSuccess; ++j) {
+        const svm_problem_t* p = &probs[j];
         e = launch_validate(p->n, p->d, p->layout, p->x, p->ldx, p->layout == SVM_DENSE_FEATURE_MAJOR, p->row_ptr,
-                            p->col, p->val, p->y, vctl, s);
-    Ctl h{};
-    int32_t nnz = 0, notpat = 1;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h, vctl, sizeof(Ctl), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && p->layout == SVM_CSR)
-        e = hipMemcpyAsync(&nnz, p->row_ptr + p->n, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return SVM_EHIP;
-    if (h.err & 1) return SVM_EINVAL;
-    if (h.err & 2) return SVM_ENONFINITE;
-    if (h.n_pos == 0 || h.n_neg == 0) return SVM_EONECLASS;
-    if (p->layout == SVM_CSR && h.max_row_nnz > 4096) return SVM_EUNSUPPORTED;
-    *out = Inspect{};
-    if (p->layout == SVM_CSR) {
-        int32_t* flag = reinterpret_cast<int32_t*>(vctl) + 40;
-        e = launch_check_pattern(nnz, p->val, flag, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(&notpat, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return SVM_EHIP;
-        out->nnz = nnz;
-        out->pattern = notpat == 0;
+                            p->col, p->val, p->y, part + (size_t)j * VAL_BLOCKS_MAX, s);
+    }
+    std::vector<ValPart> h((size_t)k * VAL_BLOCKS_MAX);
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), part, bytes, hipMemcpyDeviceToHost, s);
+    const hipError_t e2 = hipStreamSynchronize(s);
+    (void)hipFree(part);
+    if (e != hipSuccess || e2 != hipSuccess) return SVM_EHIP;
+    for (int j = 0; j < k; ++j) {
+        const ValPart v = val_sum(h.data() + (size_t)j * VAL_BLOCKS_MAX, probs[j].n);
+        if (v.flags & VAL_MALFORMED) return SVM_EINVAL;
+        if (v.flags & VAL_NONFINITE) return SVM_ENONFINITE;
+        if (v.n_pos == 0 || v.n_neg == 0) return SVM_EONECLASS;
+        if (probs[j].layout == SVM_CSR && v.max_row_nnz > 4096) return SVM_EUNSUPPORTED;
+        out[j] = Inspect{};
+        if (probs[j].layout == SVM_CSR) {
+            out[j].nnz = v.nnz;
+            out[j].pattern = !(v.flags & VAL_NOT_ONES);
+        }
     }
     return SVM_OK;
 }
@@ -602,19 +604,12 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     std::vector<int> team(k);
     std::vector<Inspect> ins(k);
     int64_t nt = 0;
-    Ctl* ictl = nullptr;
-    if (hipMalloc(&ictl, sizeof(Ctl) + 256) != hipSuccess) return SVM_ENOMEM;
+    if (const int rc = inspect(k, probs, s, ins.data())) return rc;
     for (int p = 0; p < k; ++p) {
-        const int rc = inspect(&probs[p], ictl, s, &ins[p]);
-        if (rc) {
-            (void)hipFree(ictl);
-            return rc;
-        }
         team[p] = team_size(&probs[p], ins[p], wg, params[p].grid_blocks, params[p].kernel_precision,
                             params[p].shrink_mode != SVM_SHRINK_NONE);
         nt += team[p];
     }
-    (void)hipFree(ictl);
     std::vector<size_t> off(k);
     size_t o = al(sizeof(BatchDesc) * k) + al(sizeof(BatchResult) * k) + al(sizeof(Ctl) + 256) + al(64) +
                al(sizeof(int2) * nt);
