@@ -325,7 +325,7 @@ int svm_debug_set_trace(int64_t cap, int32_t* i_up, int32_t* i_low, double* b_up
  * selection, [7] summary and completion.  NULL switches it off. */
 int svm_debug_set_profile(uint64_t* slots);
 
-/* Residency mode (0 HBM, 1 per-row state in LDS, 2 state and rows in LDS),
+/* Residency mode (0 HBM, 1 per-row state in LDS, 2 state and rows in LDS or registers),
  * workgroups and CSR lanes per row chosen by the last svm_train on this host
  * thread (host outputs, may be NULL). */
 int svm_debug_step_info(int32_t* mode, int32_t* grid_blocks, int32_t* lanes_per_row);

@@ -55,10 +55,9 @@ constexpr int DPP_BCAST31 = 0x143;  // row_bcast:31
 
 // Exact two-threshold reductions (eq:bminmax): the up side keeps the least f, the low side the
 // largest, ties to the lowest sample id.  Values are only compared, never combined, so any
-// order of reduction picks the same winner.  Each runs in two passes over the lanes: first
-// the extreme value, then the lowest id among the lanes holding it; the winner keeps its own
-// value (an f equal to the extreme can differ from it only in the sign of a zero).  Lanes
-// without a candidate hold (+inf, IDX_NONE) on the up side and (-inf, IDX_NONE) on the low side.
+// order of reduction picks the same winner, which keeps its own value (an f equal to the extreme can
+// differ from it only in the sign of a zero).  Lanes without a candidate hold (+inf, IDX_NONE) on the
+// up side and (-inf, IDX_NONE) on the low side.
 //
 // Lane moves: quad swaps and row rotations by 4 and 8 leave every lane of a 16-lane row with
 // the row's result; the two row broadcasts then carry it to lane 63 only (the other lanes of
@@ -80,11 +79,17 @@ DEV void ext_step(double& mu, double& ml) {
     mu = ou < mu ? ou : mu;
     ml = ol > ml ? ol : ml;
 }
-// (ids: the move's unwritten lanes hold IDX_NONE, so the min folds into one DPP instruction)
+// (ids and keys: the move's unwritten lanes hold the largest value, so the min folds into one DPP
+// instruction)
 template <int CTRL, int ROWS>
 DEV void idx_step(int& ju, int& jl) {
     ju = min(ju, __builtin_amdgcn_update_dpp(IDX_NONE, ju, CTRL, ROWS, 0xF, false));
     jl = min(jl, __builtin_amdgcn_update_dpp(IDX_NONE, jl, CTRL, ROWS, 0xF, false));
+}
+// High word of a key that orders doubles as unsigned integers (-0 as +0).
+DEV int order_key(double v) {
+    const int h = (int)(__double_as_longlong(v + 0.0) >> 32);
+    return h ^ ((h >> 31) & 0x7fffffff);
 }
 
 DEV double readlane_d(double v, int lane) {
@@ -94,13 +99,10 @@ DEV double readlane_d(double v, int lane) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Wave-wide two-threshold reduction; every lane returns the winners.  DPP moves and lane
-// reads only: no LDS traffic.  Needs the whole wave active.  With LANES = 16 only lanes 0-15
-// may hold candidates (the others must hold the empty entries), and the broadcasts between
-// rows are skipped.
-template <int LANES = 64>
-DEV void wave_reduce_sel(double& bu, int& iu, double& bl, int& il) {
-    static_assert(LANES == 16 || LANES == 64, "a row or the whole wave");
+// The reduction in two full passes: the extreme values, then the lowest id among the lanes that hold
+// them.  wu, wl: lanes of the winners.
+template <int LANES>
+DEV void wave_reduce_ties(double bu, int iu, double bl, int il, int& wu, int& wl) {
     constexpr int LAST = LANES - 1;   // a lane that ends with the result
     double mu = bu, ml = bl;
     ext_step<DPP_XOR1, 0xF>(mu, ml);
@@ -124,13 +126,50 @@ DEV void wave_reduce_sel(double& bu, int& iu, double& bl, int& il) {
     }
     ju = __builtin_amdgcn_readlane(ju, LAST);
     jl = __builtin_amdgcn_readlane(jl, LAST);
-    // the lanes holding the winners (in an empty side every lane holds the same empty entry)
-    const int wu = __builtin_ctzll(__ballot(iu == ju && bu == mu));
-    const int wl = __builtin_ctzll(__ballot(il == jl && bl == ml));
+    // (in an empty side every lane holds the same empty entry)
+    wu = __builtin_ctzll(__ballot(iu == ju && bu == mu));
+    wl = __builtin_ctzll(__ballot(il == jl && bl == ml));
+}
+
+// Wave-wide two-threshold reduction; every lane returns the winners, wu and wl the lanes that held
+// them.  Lane moves only: no LDS traffic.  Needs the whole wave active.  With LANES = 16 only lanes
+// 0-15 may hold candidates (the others must hold the empty entries), and the broadcasts between
+// rows are skipped.
+// It is a chain of dependent instructions, three times in every iteration of the loop, so the common
+// case is kept short: the high words of ordered keys are reduced first, one instruction a step, and
+// a side whose least high word sits in one lane is decided; only otherwise (values that agree in 20
+// bits of their fraction, ties, an empty side) do the values and ids take their two full passes.
+template <int LANES = 64>
+DEV void wave_reduce_sel(double& bu, int& iu, double& bl, int& il, int& wu, int& wl) {
+    static_assert(LANES == 16 || LANES == 64, "a row or the whole wave");
+    constexpr int LAST = LANES - 1;
+    const int ku = order_key(bu), kl = order_key(-bl);
+    int mu = ku, ml = kl;
+    idx_step<DPP_XOR1, 0xF>(mu, ml);
+    idx_step<DPP_XOR2, 0xF>(mu, ml);
+    idx_step<DPP_ROR4, 0xF>(mu, ml);
+    idx_step<DPP_ROR8, 0xF>(mu, ml);
+    if constexpr (LANES == 64) {
+        idx_step<DPP_BCAST15, 0xA>(mu, ml);
+        idx_step<DPP_BCAST31, 0xC>(mu, ml);
+    }
+    const unsigned long long eu = __ballot(ku == __builtin_amdgcn_readlane(mu, LAST));
+    const unsigned long long el = __ballot(kl == __builtin_amdgcn_readlane(ml, LAST));
+    if (((eu & (eu - 1)) | (el & (el - 1))) == 0) {
+        wu = __builtin_ctzll(eu);
+        wl = __builtin_ctzll(el);
+    } else {
+        wave_reduce_ties<LANES>(bu, iu, bl, il, wu, wl);
+    }
     bu = readlane_d(bu, wu);
     bl = readlane_d(bl, wl);
-    iu = ju;
-    il = jl;
+    iu = __builtin_amdgcn_readlane(iu, wu);
+    il = __builtin_amdgcn_readlane(il, wl);
+}
+template <int LANES = 64>
+DEV void wave_reduce_sel(double& bu, int& iu, double& bl, int& il) {
+    int wu, wl;
+    wave_reduce_sel<LANES>(bu, iu, bl, il, wu, wl);
 }
 
 // Sums of two ints over lanes 0-31 (lanes 32-63 ignored), returned in every lane: row sums by

@@ -60,7 +60,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) & ~(ALIGN - 1); }
 struct Plan {
     size_t ctl, xpack, bits, fint, status, mask, act, seg, cnt, rec, listw, listz, coef, blkcnt, counts, part,
         sumblk, out6, work, htcnt, hthmap, htbits, hthead, htnrm, httcnt, htmisc, htbhead, htbnrm, httoff, httent,
-        kcache, ktags, col16, val2, prp, total;
+        kcache, ktags, col16, val2, prp, dbg, total;
     int64_t cache_rows;   // slots of the kernel-row cache (0: none)
     int tag_grid;         // workgroups the cache tags are sized for
 };
@@ -156,6 +156,7 @@ Plan make_plan(const svm_problem_t* p, const svm_params_t* params, int64_t nnz) 
     q.col16 = take(sizeof(uint16_t) * npad);
     q.val2 = take(sizeof(float) * npad);
     q.prp = take(p->layout == SVM_CSR ? sizeof(int32_t) * (n + 1) : 0);
+    q.dbg = take(sizeof(RegDebug));
     q.total = o;
     return q;
 }
@@ -323,6 +324,7 @@ struct Solver {
     unsigned long long* ktags = nullptr;
     int cache_rows = 0;
     uint32_t epoch = 0;
+    int reg_w4 = 0, reg_r = 0;       // the loop with its rows in registers: its instance (0: svm_step.hip's)
     int kfull = 0;                   // the cache holds the whole kernel matrix
     double ms_kmatrix = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr, ev2 = nullptr, ev3 = nullptr;
@@ -560,8 +562,27 @@ struct Solver {
         a.cache_rows = cache_rows;
         a.kfull = kfull;
         a.epoch = ++epoch;   // tags of earlier launches (other active sets) never match
+        RegArgs r{};
+        if (reg_r) {
+            r.stride = lay == LAY_BITS ? a.wpr : dpad;
+            r.x = xin; r.bits = bits;
+            r.y = a.y; r.alpha = alpha; r.f = f; r.status = status;
+            r.act = act; r.seg_start = seg; r.cnt = cnt;
+            r.rec = reinterpret_cast<unsigned long long*>(rec); r.ctl = ctl;
+            r.C = a.C; r.gamma = a.gamma; r.thr = thr;
+            r.max_iter = a.max_iter; r.H = H;
+            r.spin_limit = a.spin_limit; r.work = work;
+            if (a.trace_cap || a.prof) {
+                const RegDebug d{a.trace_cap, a.tr_iu, a.tr_il, a.tr_bu, a.tr_bl, a.prof};
+                RegDebug* dd = at<RegDebug>(plan.dbg);
+                HIP_TRY(hipMemcpyAsync(dd, &d, sizeof(d), hipMemcpyHostToDevice, s));
+                HIP_TRY(hipStreamSynchronize(s));
+                r.dbg = dd;
+            }
+        }
         HIP_TRY(hipEventRecord(ev0, s));
-        HIP_TRY(launch_step(a, G, lpr, q->kernel_precision, plan_lds.total, s));
+        if (reg_r) HIP_TRY(launch_reg(r, lay, q->kernel_precision == SVM_KERNEL_FP64, reg_w4, reg_r, G, s));
+        else HIP_TRY(launch_step(a, G, lpr, q->kernel_precision, plan_lds.total, s));
         HIP_TRY(hipEventRecord(ev1, s));
         int rc = read_ctl();
         if (rc) return rc;
@@ -580,6 +601,46 @@ struct Solver {
         return SVM_OK;
     }
 };
+
+// Workgroups of svm_step.hip's loop, from per-phase timings on gfx950: one workgroup (no exchange
+// at all) up to 4096 samples; beyond that about 700 samples per workgroup (at most 11 of the
+// 16 waves hold a row, under three per SIMD), at most one workgroup per CU.  Measured: whole
+// text-like solves (n = 200,000, row cache) 7.56 / 7.42 / 7.30 / 7.16 / 7.10 s at G = 192 / 208 /
+// 224 / 240 / 256.  Bitset rows: about 390 samples per workgroup (sparse binary n = 50,000: 5.90 us
+// per iteration at G = 128, against 6.18 at 71).
+int step_grid_rule(int lay, int n, int cus) {
+    const int per = lay == LAY_BITS ? 390 : 700;
+    return n <= 4096 ? 1 : std::max(1, std::min(cus, (n + per / 2) / per));
+}
+
+// Workgroups of the loop with its rows in registers (instances of W4 16-byte words a row).
+//  * One workgroup, without an exchange, while the rows a thread then holds beyond the first take
+//    less time than the exchange (about 1.35 us; a row takes about 16 W4 + 35 instructions of a
+//    wave, two waves a SIMD): dense d = 20, n = 2000 3.48 us per iteration against 3.59 / 3.69 on
+//    4 / 8 workgroups, binary d = 300, n = 2000 about 3.5 against 4.0.  FP64 rows cost several times
+//    that: one row a thread at most.
+//  * Then 256 rows per workgroup (a wave on each SIMD) up to 64 workgroups, whose records one wave
+//    merges: binary n = 5000 4.01 us at G = 20 against 4.27 / 4.64 at 10 / 5; dense d = 128, n = 9000
+//    5.36 at 36 against 5.60 at 18.
+//  * Then 512 (one row a thread) as long as the CUs allow: mixture n = 20,000 4.02 us at G = 40
+//    against 4.34 / 4.37 / 5.11 at 80 / 29 / 16; n = 120,000 5.20 at 235 against 5.39 / 5.85 at
+//    118 / 60.  FP64 rows stay at 256: n = 3301, d = 33 6.13 us at G = 13 against 6.75 / 8.65 at 7 / 4.
+//  * Beyond, the fewest rows a thread that fit the chip: mixture n = 500,000, four: 6.9 us.
+int reg_grid_rule(bool fp64, int W4, int n, int cus) {
+    const int one = fp64 ? 1 : reg_rows_max(fp64, W4);
+    for (int r = 1; r <= one; r *= 2)
+        if (n <= r * REG_BLOCK) {
+            if ((r - 1) * (16 * W4 + 35) < 405) return 1;
+            break;
+        }
+    const int gmax = std::min(cus, REG_GRID_MAX);
+    int g = (n + 255) / 256;
+    if (g <= (fp64 ? gmax : std::min(gmax, 64))) return g;
+    for (int per = REG_BLOCK;; per *= 2) {
+        g = (n + per - 1) / per;
+        if (g <= gmax) return g;
+    }
+}
 
 int64_t heuristic_h(const svm_params_t* q, int n) {
     double h = q->shrink_kind == SVM_KIND_FIXED ? q->shrink_param : std::ceil(q->shrink_param * (double)n);
@@ -715,29 +776,30 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
     }
     const int max_mode = (q->flags & SVM_FLAG_NO_LDS_STATE) ? STEP_GLOBAL
                        : (q->flags & SVM_FLAG_NO_LDS_PAYLOAD) ? STEP_LDS_STATE : STEP_LDS_ALL;
-    // Shape rules from per-phase timings of the loop on gfx950: one workgroup (no exchange at
-    // all) up to 4096 samples; beyond that about 700 samples per workgroup (at most 11 of the
-    // 16 waves hold a row, under three per SIMD), at most one workgroup per CU.  Measured:
-    // sparse binary n = 50,000 6.42 / 6.29 us per iteration at G = 63 / 72; whole text-like
-    // solves (n = 200,000, row cache) 7.56 / 7.42 / 7.30 / 7.16 / 7.10 s at G = 192 / 208 /
-    // 224 / 240 / 256, the records being read in one memory round trip (with two, the exchange
-    // grew with G^2 and 224 was best); dense n = 500,000 15.1 us per iteration at G = 245
-    // and at 256 (two rows per lane), 16.1 at 224 (three).
     const int cus = std::max(1, device_cu_count());
     int G = q->grid_blocks;
     const TuneClass tclass{TUNE_GRID, S.lay, q->kernel_precision, S.pattern_only, q->shrink_mode != SVM_SHRINK_NONE,
                            p->n, p->d};
     if (!G) G = tuned_shape(tclass);   // measured by svm_autotune for this class
-    if (!G) {
-        // bitset rows: about 390 samples per workgroup (sparse binary n = 50,000: 5.90 us per
-        // iteration and a solve of 0.114 s at G = 128, against 6.18 us and 0.120 s at 71)
-        const int per = S.lay == LAY_BITS ? 390 : 700;
-        G = p->n <= 4096 ? 1 : std::max(1, std::min(cus, (p->n + per / 2) / per));
+    // dense and bitset rows that fit the register file stay there (svm_regloop.h)
+    if ((S.lay == LAY_DENSE || S.lay == LAY_BITS) && max_mode == STEP_LDS_ALL &&
+        (S.plan.cache_rows == 0 || S.lay == LAY_BITS)) {
+        const bool fp64 = q->kernel_precision == SVM_KERNEL_FP64;
+        const int w4 = reg_width(S.lay, S.lay == LAY_BITS ? bits_wpr(p->d) : S.dpad);
+        const int g = std::min(G ? G : reg_grid_rule(fp64, w4, p->n, cus), p->n);
+        const int r = w4 ? reg_rows(fp64, w4, (p->n + g - 1) / g) : 0;
+        if (r && g <= REG_GRID_MAX && reg_max_blocks(S.lay, fp64, w4, r) >= g) {
+            S.reg_w4 = w4;
+            S.reg_r = r;
+            G = g;
+        }
     }
+    if (!G) G = step_grid_rule(S.lay, p->n, cus);
     G = std::min(G, p->n);
     const double avg_nnz = p->layout == SVM_CSR ? (double)hrp[p->n] / (double)p->n : 0.0;
     StepLds plan{};
-    for (int tries = 0;; ++tries) {
+    if (S.reg_r) plan.mode = STEP_LDS_ALL;
+    for (int tries = 0; !S.reg_r; ++tries) {
         const int nseg_max = (p->n + G - 1) / G;
         long long nnz_seg_max = 0;
         if (!hrp.empty())
@@ -1420,8 +1482,17 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
     svm_result_t r{};
     int lay = 0, pattern = 0;
     if (target == SVM_TUNE_GRID) {
+        // around the rule of the loop that the problem takes
         const int cus = std::max(1, device_cu_count());
-        const int g0 = n <= 4096 ? 1 : std::max(1, std::min(cus, (n + 350) / 700));
+        bool pat = false;
+        if (prob->layout == SVM_CSR && (rc = csr_pattern_only(prob, reinterpret_cast<int32_t*>(f), s, &pat))) {
+            cleanup();
+            return rc;
+        }
+        const int rl = prob->layout != SVM_CSR ? LAY_DENSE : pat && prob->d <= BITS_MAX_D ? LAY_BITS : LAY_CSR_TABLE;
+        const int w4 = rl == LAY_CSR_TABLE ? 0 : reg_width(rl, rl == LAY_BITS ? bits_wpr(prob->d) : dpad_of(prob->d));
+        const bool fp64 = q.kernel_precision == SVM_KERNEL_FP64;
+        const int g0 = w4 ? reg_grid_rule(fp64, w4, n, cus) : step_grid_rule(rl, n, cus);
         for (int v : {g0 / 2, (3 * g0) / 4, g0, std::min(cus, (5 * g0) / 4), std::min(cus, (3 * g0) / 2)})
             if (v <= n) add(v);
         q.grid_blocks = cand.back();

@@ -132,6 +132,50 @@ struct StepLds {
 StepLds plan_step_lds(int lay, int d, int dpad, int max_row_nnz, int nseg_max, long long nnz_seg_max,
                       bool pattern_only, int max_mode, int G);
 
+// ---- the loop with its rows in registers (svm_regloop.h): dense rows and bitset rows
+constexpr int REG_BLOCK = 512;        // threads per workgroup: 256 vector registers a lane
+constexpr int REG_GRID_MAX = 256;
+// The test hooks' buffers, in device memory (out of the loop's scalar registers when not in use).
+struct RegDebug {
+    int64_t trace_cap;
+    int32_t* tr_iu;
+    int32_t* tr_il;
+    double* tr_bu;
+    double* tr_bl;
+    unsigned long long* prof;
+};
+struct RegArgs {
+    int32_t stride;           // dense: floats per row (dpad); bitsets: words per row (wpr)
+    const float* x;           // dense rows [n][stride]
+    const uint32_t* bits;     // or bitset rows [n][stride]
+    const int8_t* y;
+    double* alpha;
+    double* f;
+    uint8_t* status;
+    int32_t* act;             // as in StepArgs
+    const int32_t* seg_start;
+    int32_t* cnt;
+    unsigned long long* rec;  // [2][G][8] records, double-buffered by iteration parity
+    Ctl* ctl;
+    double C, gamma, thr;
+    int64_t max_iter, H;
+    unsigned long long spin_limit;
+    unsigned long long* work;
+    const RegDebug* dbg;      // or NULL
+};
+// Rows a thread can hold (1, 2 or 4) of W4 * 16 bytes each: at most 160 of the 256 registers, the rest
+// being the f, status and distances of the rows and the working set; FP64 distances take twice theirs.
+constexpr int reg_rows_max(bool fp64, int W4) { return W4 * 4 <= 40 && !fp64 ? 4 : W4 * 2 <= 40 ? 2 : 1; }
+// Row width (in 16-byte words) of the instance for rows of `stride` 4-byte words: the next that is
+// built; 0: none
+int reg_width(int lay, int stride);
+// Rows per thread (1, 2, 4) that hold nseg rows in a workgroup; 0: too many
+int reg_rows(bool fp64, int W4, int nseg);
+const void* reg_fn_dense(bool fp64, int W4, int R);
+const void* reg_fn_bits(bool fp64, int W4, int R);
+int reg_max_blocks(int lay, bool fp64, int W4, int R);
+hipError_t launch_reg(const RegArgs& a, int lay, bool fp64, int W4, int R, int G, hipStream_t s);
+
 // Kernel sums: out[a] = sum_b coef[b] * K(A_a, B_b) + bias_a, bias_a = -y_a or -beta.
 struct SumArgs {
     int32_t lay;              // LAY_DENSE, LAY_CSR_TABLE, LAY_CSR_SLOT or LAY_BITS (A and B share it)

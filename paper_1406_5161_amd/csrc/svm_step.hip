@@ -951,6 +951,46 @@ hipError_t launch_step(const StepArgs& a, int G, int lpr, int kprec, size_t lds,
     return hipLaunchCooperativeKernel(fn, dim3(G), dim3(STEP_BLOCK), args, (unsigned)lds, s);
 }
 
+// ---- the register-resident loop (instances in svm_reg_dense.hip and svm_reg_bits.hip)
+
+int reg_width(int lay, int stride) {
+    static const int dense[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32};
+    static const int bits[] = {1, 2, 3, 4, 6, 8};
+    if (lay == LAY_DENSE) {
+        for (int w : dense)
+            if (4 * w >= stride) return w;
+    } else if (lay == LAY_BITS) {
+        for (int w : bits)
+            if (4 * w >= stride) return w;
+    }
+    return 0;
+}
+
+int reg_rows(bool fp64, int W4, int nseg) {
+    for (int r = 1; r <= reg_rows_max(fp64, W4); r *= 2)
+        if (nseg <= r * REG_BLOCK) return r;
+    return 0;
+}
+
+static const void* reg_fn(int lay, bool fp64, int W4, int R) {
+    return lay == LAY_BITS ? reg_fn_bits(fp64, W4, R) : reg_fn_dense(fp64, W4, R);
+}
+
+int reg_max_blocks(int lay, bool fp64, int W4, int R) {
+    const void* fn = reg_fn(lay, fp64, W4, R);
+    int nb = 0;
+    if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, REG_BLOCK, 0) != hipSuccess) return 0;
+    return nb * device_cu_count();
+}
+
+hipError_t launch_reg(const RegArgs& a, int lay, bool fp64, int W4, int R, int G, hipStream_t s) {
+    const void* fn = reg_fn(lay, fp64, W4, R);
+    if (!fn || G < 1 || G > REG_GRID_MAX) return hipErrorInvalidValue;
+    RegArgs copy = a;
+    void* args[] = {&copy};
+    return hipLaunchCooperativeKernel(fn, dim3(G), dim3(REG_BLOCK), args, 0, s);
+}
+
 int step_max_blocks(int lay, int lpr, int kprec, int mode, size_t lds, bool cache) {
     const void* fn = pick(lay, kprec, mode, lpr, cache);
     if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
