@@ -82,7 +82,12 @@ DEV BatchDesc uniform_desc(const BatchDesc& S) {
 // group sum over `lpr` consecutive lanes (lpr a power of two <= 64)
 template <typename T>
 DEV T group_sum(T v, int lpr) {
-    for (int off = 1; off < lpr; off <<= 1) v += __shfl_xor(v, off);
+    if (lpr > 1) v = xor_add<1>(v);
+    if (lpr > 2) v = xor_add<2>(v);
+    if (lpr > 4) v = xor_add<4>(v);
+    if (lpr > 8) v = xor_add<8>(v);
+    if (lpr > 16) v = xor_add<16>(v);
+    if (lpr > 32) v = xor_add<32>(v);
     return v;
 }
 

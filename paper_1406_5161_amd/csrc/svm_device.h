@@ -200,18 +200,72 @@ DEV float wave_sum_dpp(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-template <typename T>
-DEV T wave_sum(T v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+// v + v of lane ^ OFF by lane moves: quad swaps, row shifts of four lanes into the banks they are for,
+// a rotation by eight, and the swaps between rows and half waves (an LDS permutation, which a general
+// lane shuffle compiles to, takes about ten times as long in a chain of dependent steps).
+template <int OFF>
+DEV void xor_lanes(int v, int& a, int& b) {   // {a, b} = {v, v of lane ^ OFF} in either order
+    if constexpr (OFF == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+        a = (int)r[0];
+        b = (int)r[1];
+    } else if constexpr (OFF == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+        a = (int)r[0];
+        b = (int)r[1];
+    } else {
+        a = v;
+        if constexpr (OFF == 8) b = __builtin_amdgcn_update_dpp(0, v, DPP_ROR8, 0xF, 0xF, false);
+        else if constexpr (OFF == 4) {
+            b = __builtin_amdgcn_update_dpp(0, v, 0x104 /* row_shl:4 */, 0xF, 0x5, false);
+            b = __builtin_amdgcn_update_dpp(b, v, 0x114 /* row_shr:4 */, 0xF, 0xA, false);
+        } else if constexpr (OFF == 2) b = __builtin_amdgcn_update_dpp(0, v, DPP_XOR2, 0xF, 0xF, false);
+        else b = __builtin_amdgcn_update_dpp(0, v, DPP_XOR1, 0xF, 0xF, false);
+    }
+}
+template <int OFF, typename T>
+DEV T xor_add(T v) {
+    if constexpr (sizeof(T) == 4) {
+        int a, b;
+        xor_lanes<OFF>(__builtin_bit_cast(int, v), a, b);
+        return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
+    } else {
+        const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+        int al, bl, ah, bh;
+        xor_lanes<OFF>((int)(unsigned)x, al, bl);
+        xor_lanes<OFF>((int)(unsigned)(x >> 32), ah, bh);
+        return __builtin_bit_cast(T, ((unsigned long long)(unsigned)ah << 32) | (unsigned)al) +
+               __builtin_bit_cast(T, ((unsigned long long)(unsigned)bh << 32) | (unsigned)bl);
+    }
+}
+
+// Sum over the N lanes of a group (N a power of two), widest step first.
+template <int N, typename T>
+DEV T lanes_sum(T v) {
+    if constexpr (N > 32) v = xor_add<32>(v);
+    if constexpr (N > 16) v = xor_add<16>(v);
+    if constexpr (N > 8) v = xor_add<8>(v);
+    if constexpr (N > 4) v = xor_add<4>(v);
+    if constexpr (N > 2) v = xor_add<2>(v);
+    if constexpr (N > 1) v = xor_add<1>(v);
     return v;
 }
+template <typename T>
+DEV T wave_sum(T v) { return lanes_sum<64>(v); }
 
 // FP32 kernel values: e^v as 2^(v log2 e) on the hardware base-2 exponential (about 1 ulp; the
 // product adds one rounding, an error of the same order as forming v = -gamma d^2 in FP32).
 // Results below the smallest normal float may flush to 0.
 DEV float kexp(float v) { return __builtin_amdgcn_exp2f(v * 1.44269504088896341f); }
 DEV double kexp(double v) { return exp(v); }
+
+// LDS written by lanes of a wave, read by others of the same wave: its LDS accesses are executed in
+// order, so only the compiler has to keep them there.
+DEV void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 DEV double ld_agent(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 DEV void st_agent(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -220,6 +274,14 @@ DEV unsigned long long ld_agent(const unsigned long long* p) {
 }
 DEV void st_agent(unsigned long long* p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Words that only threads of one workgroup read and write.
+DEV unsigned long long ld_own(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+DEV void st_own(unsigned long long* p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // LDS the block reductions below need: SEL_LDS(BLOCK) doubles and as many ints.
@@ -265,17 +327,6 @@ template <int BLOCK>
 DEV void block_reduce_sel(double& bu, int& iu, double& bl, int& il, double* s_v, int* s_i) {
     block_reduce_sel_all<BLOCK>(bu, iu, bl, il, s_v, s_i);
     __syncthreads();
-}
-
-// Block-wide reduction whose result only wave 0 needs: the wave results go to LDS, one
-// barrier, then wave 0 alone reduces them; the other waves return at once.  Every lane of
-// wave 0 holds the result; other lanes keep their own candidates.  The caller must not
-// overwrite s_v / s_i before the next barrier.
-template <int BLOCK>
-DEV void block_reduce_sel_wave0(double& bu, int& iu, double& bl, int& il, double* s_v, int* s_i) {
-    waves_to_lds<BLOCK>(bu, iu, bl, il, s_v, s_i);
-    __syncthreads();
-    if ((threadIdx.x >> 6) == 0) wave_reduce_waves<BLOCK>(bu, iu, bl, il, s_v, s_i);
 }
 
 // ------------------------------------------------------------------ pair update (eq:alphaup, eq:rho)

@@ -799,38 +799,69 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
     const double avg_nnz = p->layout == SVM_CSR ? (double)hrp[p->n] / (double)p->n : 0.0;
     StepLds plan{};
     if (S.reg_r) plan.mode = STEP_LDS_ALL;
-    for (int tries = 0; !S.reg_r; ++tries) {
-        const int nseg_max = (p->n + G - 1) / G;
-        long long nnz_seg_max = 0;
-        if (!hrp.empty())
-            for (int b = 0; b < G; ++b) {
-                const int s0 = (int)(((long long)p->n * b) / G), s1 = (int)(((long long)p->n * (b + 1)) / G);
-                nnz_seg_max = std::max<long long>(nnz_seg_max, hrp[s1] - hrp[s0]);
+    // the residency, lanes per row and number of workgroups (at most g) that fit the device; mode
+    // at most mmax
+    auto shape = [&](int& g, int mmax, int lpr_fixed) -> int {
+        for (int tries = 0;; ++tries) {
+            const int nseg_max = (p->n + g - 1) / g;
+            long long nnz_seg_max = 0;
+            if (!hrp.empty())
+                for (int b = 0; b < g; ++b) {
+                    const int s0 = (int)(((long long)p->n * b) / g), s1 = (int)(((long long)p->n * (b + 1)) / g);
+                    nnz_seg_max = std::max<long long>(nnz_seg_max, hrp[s1] - hrp[s0]);
+                }
+            plan = plan_step_lds(S.lay, S.d, S.dpad, S.max_row_nnz, nseg_max, nnz_seg_max, S.pattern_only, mmax, g);
+            if (plan.total > STEP_LDS_BUDGET) {
+                // the records' LDS copy grows with G: where the pair rows leave too little room for
+                // it, fewer workgroups (one workgroup has no records at all)
+                if (g == 1 || plan.rec_off > STEP_LDS_BUDGET || tries > 8) return SVM_EUNSUPPORTED;
+                const size_t rec_room = STEP_LDS_BUDGET - plan.rec_off;
+                const int gfit = (int)(rec_room / (sizeof(uint32_t) * REC_LDS_STRIDE)) - 4;
+                g = std::max(1, std::min(g - 1, gfit));
+                continue;
             }
-        plan = plan_step_lds(S.lay, S.d, S.dpad, S.max_row_nnz, nseg_max, nnz_seg_max, S.pattern_only, max_mode, G);
-        if (plan.total > STEP_LDS_BUDGET) {
-            // the records' LDS copy grows with G: where the pair rows leave too little room for
-            // it, fewer workgroups (one workgroup has no records at all)
-            if (G == 1 || plan.rec_off > STEP_LDS_BUDGET || tries > 8) return SVM_EUNSUPPORTED;
-            const size_t rec_room = STEP_LDS_BUDGET - plan.rec_off;
-            const int gfit = (int)(rec_room / (sizeof(uint32_t) * REC_LDS_STRIDE)) - 4;
-            G = std::max(1, std::min(G - 1, gfit));
-            continue;
+            if (p->layout == SVM_CSR && S.lay != LAY_BITS && !q->lanes_per_row) {
+                // rows in LDS: few lanes per row (short LDS chains, no cross-lane reduction);
+                // rows from HBM: enough lanes for coalesced row reads
+                int l = 1;
+                if (lpr_fixed) l = lpr_fixed;
+                else if (plan.mode == STEP_LDS_ALL) l = avg_nnz < 48 ? 2 : 4;
+                else while (l < 32 && 16.0 * l <= avg_nnz) l *= 2;
+                S.lpr = l;
+            }
+            const bool cache = S.plan.cache_rows > 0 && step_cache_capable(S.lay, plan.mode);
+            const int maxG = std::min(MAX_GRID, step_max_blocks(S.lay, S.lpr, q->kernel_precision, plan.mode,
+                                                                plan.total, cache));
+            if (maxG < 1) return SVM_EUNSUPPORTED;
+            if (g <= maxG || tries > 4) { g = std::min(g, maxG); return SVM_OK; }
+            g = maxG;
         }
-        if (p->layout == SVM_CSR && S.lay != LAY_BITS && !q->lanes_per_row) {
-            // rows in LDS: few lanes per row (short LDS chains, no cross-lane reduction);
-            // rows from HBM: enough lanes for coalesced row reads
-            int l = 1;
-            if (plan.mode == STEP_LDS_ALL) l = avg_nnz < 48 ? 2 : 4;
-            else while (l < 32 && 16.0 * l <= avg_nnz) l *= 2;
-            S.lpr = l;
+    };
+    if (!S.reg_r) {
+        const bool chosen = q->grid_blocks || tuned_shape(tclass);
+        if ((rc = shape(G, max_mode, 0))) return rc;
+        if (!chosen && p->layout == SVM_CSR && S.lay != LAY_BITS) {
+            // The residency and lanes per row set the order in which a row's products are added, so
+            // they stay those of that grid; the rows then spread over as many workgroups as hold
+            // them in one pass (1024 / lanes rows each).  Text-like n = 20,000, eight lanes, row
+            // cache: 9.4 / 9.8 / 10.4 / 13.5 us per iteration at G = 192 / 128 / 64 / 29 (the grid of
+            // 700 rows each); two passes or fewer on one workgroup need no exchange.
+            const int per = STEP_BLOCK / S.lpr;
+            int g2 = std::max(1, std::min(cus, (p->n + per - 1) / per));
+            if (g2 > G && !(G == 1 && p->n <= 2 * per)) {
+                const StepLds was = plan;
+                const int lpr = S.lpr;
+                // (state in LDS or not makes no difference to the order)
+                const bool rows_lds = was.mode == STEP_LDS_ALL;
+                if (shape(g2, rows_lds ? max_mode : std::min<int>(max_mode, STEP_LDS_STATE), lpr) == SVM_OK &&
+                    (plan.mode == STEP_LDS_ALL) == rows_lds && g2 > G) {
+                    G = g2;
+                } else {
+                    plan = was;
+                    S.lpr = lpr;
+                }
+            }
         }
-        const bool cache = S.plan.cache_rows > 0 && step_cache_capable(S.lay, plan.mode);
-        const int maxG = std::min(MAX_GRID, step_max_blocks(S.lay, S.lpr, q->kernel_precision, plan.mode, plan.total,
-                                                            cache));
-        if (maxG < 1) return SVM_EUNSUPPORTED;
-        if (G <= maxG || tries > 4) { G = std::min(G, maxG); break; }
-        G = maxG;
     }
     S.G = G;
     S.plan_lds = plan;

@@ -45,14 +45,6 @@ DEV double rec8_double(unsigned long long lo48, unsigned long long hi) {
     return __longlong_as_double((long long)((lo48 & REC8_MASK) | (hi << 48)));
 }
 
-// LDS written by lanes of a wave, read by others of the same wave: its LDS accesses are executed in
-// order, so only the compiler has to keep them there.
-DEV void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // A value that the compiler takes as formed at this place and unknown from here on.
 template <typename T>
 DEV void pin(T& v) { asm volatile("" : "+v"(v)); }

@@ -98,10 +98,13 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
     __shared__ int s_i[SEL_LDS(BLOCK)];
     __shared__ int s_wc[NW];
     __shared__ double s_pair[4];     // K_ul, |u|^2, |l|^2
-    __shared__ double s_sel[4];
-    __shared__ int s_seli[3];
+    // merged records, one entry per 64 of them (empty ones keep their initial values)
+    constexpr int NM = MAX_GRID / 64;
+    __shared__ double m_v[2 * NM], m_a[2 * NM];
+    __shared__ int m_i[2 * NM], m_c[NM];
+    __shared__ unsigned long long m_e[2 * NM];
+    __shared__ int s_abort;
     __shared__ int s_prev_n;
-    __shared__ unsigned long long s_ext[2];
     __shared__ int s_cache[4];       // kernel-row cache: slot of i_up, slot of i_low, hit up, hit low
 
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -124,7 +127,17 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
         for (int k = tid; k < A.d; k += BLOCK) slot[k] = 0;
         if (tid == 0) pairv[0] = make_float2(0.f, 0.f);
     }
-    if (tid == 0) s_prev_n = 0;
+    if (tid == 0) {
+        s_prev_n = 0;
+        s_abort = 0;
+    }
+    if (tid < 2 * NM) {
+        m_v[tid] = tid < NM ? INFINITY : -INFINITY;
+        m_a[tid] = 0.0;
+        m_i[tid] = IDX_NONE;
+        m_e[tid] = 0;
+        m_c[tid % NM] = 0;
+    }
 
     // ---- this workgroup's segment and where its rows live during the launch
     const int seg0 = A.seg_start[blk];
@@ -261,27 +274,20 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
             A.tr_iu[iter] = iu; A.tr_il[iter] = il; A.tr_bu[iter] = bu; A.tr_bl[iter] = bl;
         }
         // ---- 1. the working pair: labels, rows into LDS (alpha came with the records)
+        // kernel rows of the pair from the cache: this workgroup's tags name the sample whose row (over
+        // this segment) each slot holds.  One thread's loads of them are in flight while the rows are
+        // staged (only this workgroup reads and writes them: its CU's caches serve them).  With the
+        // whole kernel matrix in the cache every row is there and K_ul too: nothing is staged.
+        int c_slots[2] = {iu, il};
+        unsigned long long c_tags[2] = {0, 0};
         if constexpr (CACHE) {
-            // kernel rows of the pair from the cache: this workgroup's tags name the sample whose
-            // row (over this segment) each slot holds; looked up by wave 1 while wave 0 (or the
-            // whole workgroup) stages the rows.  With the whole kernel matrix in the cache every
-            // row is there and K_ul too: nothing is staged.
-            if (tid == 64) {
-                if (kfull) {
-                    s_cache[0] = iu;
-                    s_cache[1] = il;
-                    s_cache[2] = 1;
-                    s_cache[3] = 1;
-                } else {
-                    const int S = A.cache_rows;
-                    const int su = iu % S, sl = il % S;
-                    const unsigned long long* tg = A.tags + (size_t)blk * S;
-                    const unsigned long long ep = (unsigned long long)A.epoch << 32;
-                    s_cache[0] = su;
-                    s_cache[1] = sl;
-                    s_cache[2] = ld_agent(tg + su) == (ep | (unsigned)iu);
-                    s_cache[3] = ld_agent(tg + sl) == (ep | (unsigned)il);
-                }
+            if (tid == 64 && !kfull) {
+                const int S = A.cache_rows;
+                const unsigned long long* tg = A.tags + (size_t)blk * S;
+                c_slots[0] = iu % S;
+                c_slots[1] = il % S;
+                c_tags[0] = ld_own(tg + c_slots[0]);
+                c_tags[1] = ld_own(tg + c_slots[1]);
             }
             if (kfull && tid == 0) s_pair[0] = (double)reinterpret_cast<const KT*>(A.cache)[(size_t)iu * A.n + il];
         }
@@ -419,6 +425,15 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
                     s_pair[1] = (double)su;
                     s_pair[2] = (double)sl2;
                 }
+            }
+        }
+        if constexpr (CACHE) {
+            if (tid == 64) {
+                const unsigned long long ep = (unsigned long long)A.epoch << 32;
+                s_cache[0] = c_slots[0];
+                s_cache[1] = c_slots[1];
+                s_cache[2] = kfull || c_tags[0] == (ep | (unsigned)iu);
+                s_cache[3] = kfull || c_tags[1] == (ep | (unsigned)il);
             }
         }
         __syncthreads();
@@ -583,12 +598,9 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
                             }
                         }
                     }
-#pragma unroll
-                    for (int off = LPR / 2; off > 0; off >>= 1) {
-                        nn += __shfl_xor(nn, off);
-                        su += __shfl_xor(su, off);
-                        sl2 += __shfl_xor(sl2, off);
-                    }
+                    nn = lanes_sum<LPR>(nn);
+                    su = lanes_sum<LPR>(su);
+                    sl2 = lanes_sum<LPR>(sl2);
                     du2 = nn + nuu - (KT)2 * su;
                     dl2 = nn + nll - (KT)2 * sl2;
                     if (du2 < (KT)0) du2 = (KT)0;
@@ -640,39 +652,45 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
             if (tid == 0) {
                 unsigned long long* tg = A.tags + (size_t)A.cache_rows * blk;
                 const unsigned long long ep = (unsigned long long)A.epoch << 32;
-                if (c_stu) st_agent(tg + c_su, ep | (unsigned)iu);
-                if (c_stl) st_agent(tg + c_sl, ep | (unsigned)il);
+                if (c_stu) st_own(tg + c_su, ep | (unsigned)iu);
+                if (c_stl) st_own(tg + c_sl, ep | (unsigned)il);
                 if (c_hu && c_hl) ++cache_both;
             }
         }
         lap(1);
 
-        block_reduce_sel_wave0<BLOCK>(cbu, ciu, cbl, cil, s_v, s_i);   // wave 0 publishes
+        waves_to_lds<BLOCK>(cbu, ciu, cbl, cil, s_v, s_i);
+        __syncthreads();
         // alpha and CSR extent of this workgroup's candidates: its own rows, which no other
-        // workgroup writes, so they travel in the records instead of being re-read later
+        // workgroup writes, so they travel in the records instead of being re-read later.  Wave 0
+        // reads those of every wave's winners while it reduces them, and publishes
         double cau = 0.0, cal = 0.0;
         unsigned long long ceu = 0, cel = 0;
-        if (wid == 0) {   // every lane of wave 0: the record's words are stored one per lane
-            if (ciu != IDX_NONE) {
-                if constexpr (MODE == STEP_GLOBAL) cau = ld_agent(A.alpha + ciu);
-                else cau = AL[ciu - seg0];
+        if (wid == 0) {
+            const bool in = lane < NW;
+            cbu = in ? s_v[lane] : INFINITY;
+            ciu = in ? s_i[lane] : IDX_NONE;
+            cbl = in ? s_v[NW + lane] : -INFINITY;
+            cil = in ? s_i[NW + lane] : IDX_NONE;
+            auto own = [&](int i, double& a, unsigned long long& e) {
+                if (i == IDX_NONE) return;
+                if constexpr (MODE == STEP_GLOBAL) a = ld_agent(A.alpha + i);
+                else a = AL[i - seg0];
                 if constexpr (CSR) {
                     unsigned p0, p1;
-                    if constexpr (MODE == STEP_GLOBAL) { p0 = (unsigned)A.row_ptr[ciu]; p1 = (unsigned)A.row_ptr[ciu + 1]; }
-                    else { p0 = (unsigned)(gbase + OFF[ciu - seg0]); p1 = (unsigned)(gbase + OFF[ciu - seg0 + 1]); }
-                    ceu = (unsigned long long)p0 | ((unsigned long long)p1 << 32);
+                    if constexpr (MODE == STEP_GLOBAL) { p0 = (unsigned)A.row_ptr[i]; p1 = (unsigned)A.row_ptr[i + 1]; }
+                    else { p0 = (unsigned)(gbase + OFF[i - seg0]); p1 = (unsigned)(gbase + OFF[i - seg0 + 1]); }
+                    e = (unsigned long long)p0 | ((unsigned long long)p1 << 32);
                 }
-            }
-            if (cil != IDX_NONE) {
-                if constexpr (MODE == STEP_GLOBAL) cal = ld_agent(A.alpha + cil);
-                else cal = AL[cil - seg0];
-                if constexpr (CSR) {
-                    unsigned p0, p1;
-                    if constexpr (MODE == STEP_GLOBAL) { p0 = (unsigned)A.row_ptr[cil]; p1 = (unsigned)A.row_ptr[cil + 1]; }
-                    else { p0 = (unsigned)(gbase + OFF[cil - seg0]); p1 = (unsigned)(gbase + OFF[cil - seg0 + 1]); }
-                    cel = (unsigned long long)p0 | ((unsigned long long)p1 << 32);
-                }
-            }
+            };
+            own(ciu, cau, ceu);
+            own(cil, cal, cel);
+            int wu, wl;
+            wave_reduce_sel<(NW <= 16 ? 16 : 64)>(cbu, ciu, cbl, cil, wu, wl);
+            cau = readlane_d(cau, wu);
+            cal = readlane_d(cal, wl);
+            ceu = (unsigned long long)__double_as_longlong(readlane_d(__longlong_as_double((long long)ceu), wu));
+            cel = (unsigned long long)__double_as_longlong(readlane_d(__longlong_as_double((long long)cel), wl));
         }
         // ---- 3. exchange (the paper's Allreduce of the b's): every workgroup stores its record
         // as tag-validated words and reads everybody's record; no barrier, no fence, no atomic RMW
@@ -752,7 +770,9 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
                     }
                 }
             }
-            if (__syncthreads_or(ab)) {
+            if (ab) s_abort = 1;
+            __syncthreads();
+            if (s_abort) {
                 if (tid == 0) __hip_atomic_store(&ctl->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 exit_reason = EXIT_ABORT;
                 break;
@@ -773,76 +793,62 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
                 rel = ((unsigned long long)v[14] << 32) | v[13];
             }
             lap(3);
-            // reduce (value, id) and the record holding each winner publishes its payload
-            // (alpha, CSR extent); with at most 64 records wave 0 holds them all
-            const int myiu = riu, myil = ril;
-            if (G <= 64) {
-                if (wid == 0) {
-                    const long long csum = do_shrink ? wave_sum(rcnt) : 0;
-                    wave_reduce_sel(rbu, riu, rbl, ril);
-                    if (tid < G) {
-                        if (myiu != IDX_NONE && myiu == riu) { s_sel[2] = rau; s_ext[0] = reu; }
-                        if (myil != IDX_NONE && myil == ril) { s_sel[3] = ral; s_ext[1] = rel; }
-                    }
-                    if (tid == 0) {
-                        s_sel[0] = rbu; s_sel[1] = rbl;
-                        s_seli[0] = riu; s_seli[1] = ril;
-                        if (do_shrink) s_seli[2] = (int)csum;
-                    }
-                }
-            } else {
-                // waves 0 .. NR-1 hold 64 records each: reduce within them, then combine NR values
-                const int NR = (G + 63) / 64;
-                if (wid < NR) {
-                    const long long csum = do_shrink ? wave_sum(rcnt) : 0;
-                    wave_reduce_sel(rbu, riu, rbl, ril);
-                    if (lane == 0) {
-                        s_v[wid] = rbu; s_i[wid] = riu;
-                        s_v[NW + wid] = rbl; s_i[NW + wid] = ril;
-                        s_wc[wid] = (int)csum;
-                    }
-                }
-                __syncthreads();
-                double xbu = s_v[0], xbl = s_v[NW];
-                int xiu = s_i[0], xil = s_i[NW];
-                for (int w = 1; w < NR; ++w) {
-                    if (better_up(s_v[w], s_i[w], xbu, xiu)) { xbu = s_v[w]; xiu = s_i[w]; }
-                    if (better_low(s_v[NW + w], s_i[NW + w], xbl, xil)) { xbl = s_v[NW + w]; xil = s_i[NW + w]; }
-                }
-                if (tid < G) {
-                    if (myiu != IDX_NONE && myiu == xiu) { s_sel[2] = rau; s_ext[0] = reu; }
-                    if (myil != IDX_NONE && myil == xil) { s_sel[3] = ral; s_ext[1] = rel; }
-                }
-                if (tid == 0) {
-                    s_sel[0] = xbu; s_sel[1] = xbl;
-                    s_seli[0] = xiu; s_seli[1] = xil;
-                    if (do_shrink) {
-                        long long c = 0;
-                        for (int w = 0; w < NR; ++w) c += s_wc[w];
-                        s_seli[2] = (int)c;
-                    }
+            // 64 records per wave, each wave's winners with their payload (alpha, CSR extent) into LDS;
+            // after one barrier every thread combines them
+            const int NR = (G + 63) / 64;
+            if (wid < NR) {
+                const long long csum = do_shrink ? wave_sum(rcnt) : 0;
+                int wu, wl;
+                wave_reduce_sel(rbu, riu, rbl, ril, wu, wl);
+                rau = readlane_d(rau, wu);
+                ral = readlane_d(ral, wl);
+                reu = (unsigned long long)__double_as_longlong(readlane_d(__longlong_as_double((long long)reu), wu));
+                rel = (unsigned long long)__double_as_longlong(readlane_d(__longlong_as_double((long long)rel), wl));
+                if (lane == 0) {
+                    m_v[wid] = rbu; m_v[NM + wid] = rbl;
+                    m_a[wid] = rau; m_a[NM + wid] = ral;
+                    m_i[wid] = riu; m_i[NM + wid] = ril;
+                    m_e[wid] = reu; m_e[NM + wid] = rel;
+                    m_c[wid] = (int)csum;
                 }
             }
+            __syncthreads();
         } else {
             if (tid == 0) {
-                s_sel[0] = cbu; s_sel[1] = cbl; s_sel[2] = cau; s_sel[3] = cal;
-                s_seli[0] = ciu; s_seli[1] = cil;
-                s_seli[2] = nrows;
-                s_ext[0] = ceu; s_ext[1] = cel;
+                m_v[0] = cbu; m_v[NM] = cbl; m_a[0] = cau; m_a[NM] = cal;
+                m_i[0] = ciu; m_i[NM] = cil;
+                m_e[0] = ceu; m_e[NM] = cel;
+                m_c[0] = nrows;
             }
             lap(2);
+            __syncthreads();
         }
-        __syncthreads();
-        bu = s_sel[0];
-        bl = s_sel[1];
-        au = s_sel[2];
-        al = s_sel[3];
-        ext_u = s_ext[0];
-        ext_l = s_ext[1];
-        iu = s_seli[0] == IDX_NONE ? -1 : s_seli[0];
-        il = s_seli[1] == IDX_NONE ? -1 : s_seli[1];
+        bu = m_v[0]; au = m_a[0]; iu = m_i[0]; ext_u = m_e[0];
+        bl = m_v[NM]; al = m_a[NM]; il = m_i[NM]; ext_l = m_e[NM];
+        int n_tot = m_c[0];
+        // (up to four entries straight through, as on one workgroup per CU; the rest, on larger
+        // requested grids, in a loop)
+        auto take = [&](int w) {
+            const double vu = m_v[w], vl = m_v[NM + w], qu = m_a[w], ql = m_a[NM + w];
+            const unsigned long long eu = m_e[w], el = m_e[NM + w];
+            const int xu = m_i[w], xl = m_i[NM + w];
+            const bool tu = better_up(vu, xu, bu, iu), tl = better_low(vl, xl, bl, il);
+            bu = tu ? vu : bu; au = tu ? qu : au; iu = tu ? xu : iu; ext_u = tu ? eu : ext_u;
+            bl = tl ? vl : bl; al = tl ? ql : al; il = tl ? xl : il; ext_l = tl ? el : ext_l;
+            n_tot += m_c[w];
+        };
+        if (G > 64) {
+            take(1);
+            take(2);
+            take(3);
+            for (int w = 4; 64 * w < G; ++w) take(w);
+        }
+        iu = __builtin_amdgcn_readfirstlane(iu);
+        il = __builtin_amdgcn_readfirstlane(il);
+        if (iu == IDX_NONE) iu = -1;
+        if (il == IDX_NONE) il = -1;
         if (do_shrink) {
-            const long long tot = s_seli[2];
+            const long long tot = n_tot;
             shrunk += n_act_total - tot;
             n_act_total = tot;
             ++passes;
