@@ -253,6 +253,17 @@ DEV T lanes_sum(T v) {
 template <typename T>
 DEV T wave_sum(T v) { return lanes_sum<64>(v); }
 
+// Inclusive sum over the lanes up to this one (whole wave active).
+DEV int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, DPP_BCAST15, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, DPP_BCAST31, 0xC, 0xF, false);
+    return v;
+}
+
 // FP32 kernel values: e^v as 2^(v log2 e) on the hardware base-2 exponential (about 1 ulp; the
 // product adds one rounding, an error of the same order as forming v = -gamma d^2 in FP32).
 // Results below the smallest normal float may flush to 0.

@@ -9,7 +9,6 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
-#include <mutex>
 #include <vector>
 
 #include "svm_internal.h"
@@ -163,45 +162,11 @@ Plan make_plan(const svm_problem_t* p, const svm_params_t* params, int64_t nnz) 
 
 // The H most frequent columns of a CSR training set (ties to the lower column id) become the
 // head: hmap / hbits on the device.
-// Host staging of the head selection: fixed arrays (the column count is at most HT_MAX_D), so
-// choosing a head allocates nothing; one call at a time uses them.
-struct HeadStage {
-    std::mutex m;
-    int32_t cnt[HT_MAX_D + 1];
-    int32_t order[HT_MAX_D + 1];
-    int32_t hmap[HT_MAX_D + 1];
-    uint32_t bits[HT_MAX_WORDS];
-};
-HeadStage& head_stage() {
-    static HeadStage h;
-    return h;
-}
-
-int ht_choose_head(const svm_problem_t* p, int H, const HtBufs& b, hipStream_t s) {
+int ht_choose_head(const svm_problem_t* p, int64_t nnz, int H, const HtBufs& b, hipStream_t s) {
     if (p->d > HT_MAX_D) return SVM_EUNSUPPORTED;
-    int32_t nnz = 0;
-    HIP_TRY(hipMemcpyAsync(&nnz, p->row_ptr + p->n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemsetAsync(b.cnt, 0, sizeof(int32_t) * (size_t)p->d, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    HIP_TRY(launch_col_count(nnz, p->col, b.cnt, s));
-    HeadStage& st = head_stage();
-    std::lock_guard<std::mutex> lock(st.m);
-    int32_t* cnt = st.cnt;
-    HIP_TRY(hipMemcpyAsync(cnt, b.cnt, sizeof(int32_t) * (size_t)p->d, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    for (int c = 0; c < p->d; ++c) st.order[c] = c;
-    const int h = std::min(H, p->d);
-    std::partial_sort(st.order, st.order + h, st.order + p->d,
-                      [cnt](int a, int b) { return cnt[a] != cnt[b] ? cnt[a] > cnt[b] : a < b; });
-    for (int c = 0; c < p->d; ++c) st.hmap[c] = -1;
-    for (int w = 0; w < HT_MAX_WORDS; ++w) st.bits[w] = 0u;
-    for (int k = 0; k < h; ++k) {
-        st.hmap[st.order[k]] = k;
-        st.bits[st.order[k] >> 5] |= 1u << (st.order[k] & 31);
-    }
-    HIP_TRY(hipMemcpyAsync(b.hmap, st.hmap, sizeof(int32_t) * (size_t)p->d, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(b.hbits, st.bits, sizeof(uint32_t) * HT_MAX_WORDS, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(launch_col_count(nnz, p->d, p->col, b.cnt, s));
+    HIP_TRY(launch_ht_choose(p->d, H, b.cnt, b.hmap, b.hbits, s));
     return SVM_OK;
 }
 
@@ -229,10 +194,18 @@ int ht_tile_rows(int na, const int32_t* alist, const int32_t* tcnt, int32_t* mis
     return SVM_OK;
 }
 
+// Splits of the sweep: the number for which the last round of workgroups (one per CU) ends first, a
+// workgroup's table costing about as much as three chunks of the sweep.
 int ht_nsplit(int na, int rows, int nb) {
-    const int blocks = (na + rows - 1) / rows;
-    int ns = std::max(1, std::min(NSPLIT_MAX, (512 + blocks - 1) / blocks));
-    return std::min(ns, std::max(1, nb / 256));
+    const long long blocks = (na + rows - 1) / rows, chunks = (nb + HT_CHUNK - 1) / HT_CHUNK;
+    const long long cus = std::max(1, device_cu_count());
+    int best = 1;
+    long long cost = 0;
+    for (int ns = 1; ns <= std::min<long long>(NSPLIT_MAX, std::max<long long>(1, chunks)); ++ns) {
+        const long long c = ((blocks * ns + cus - 1) / cus) * ((chunks + ns - 1) / ns + 3);
+        if (ns == 1 || c < cost) { cost = c; best = ns; }
+    }
+    return best;
 }
 
 int check_problem(const svm_problem_t* p, bool need_labels) {
@@ -738,7 +711,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
             S.ht.bnrm = S.at<float>(S.plan.htbnrm);
             S.ht.toff = S.at<int32_t>(S.plan.httoff);
             S.ht.tent = S.at<uint2>(S.plan.httent);
-            if ((rc = ht_choose_head(p, S.ht_H, S.ht, s))) return rc;
+            if ((rc = ht_choose_head(p, nnz_all, S.ht_H, S.ht, s))) return rc;
             HIP_TRY(hipMemsetAsync(S.ht.misc + 3, 0, sizeof(int32_t), s));
             HIP_TRY(launch_ht_split(p->n, S.ht_H, p->row_ptr, p->col, p->val, S.ht.hmap, S.ht.head, S.ht.nrm,
                                     S.ht.tcnt, (unsigned*)(S.ht.misc + 3), s));
@@ -1311,7 +1284,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
         float* qhead = (float*)(ws + P.qhead);
         float* qnrm = (float*)(ws + P.qnrm);
         int32_t* qtcnt = (int32_t*)(ws + P.qtcnt);
-        int rc = ht_choose_head(train, H, b, s);
+        int rc = ht_choose_head(train, tnnz, H, b, s);
         if (rc) return rc;
         HIP_TRY(hipMemsetAsync(b.misc + 3, 0, sizeof(int32_t), s));
         HIP_TRY(launch_ht_split(n, H, train->row_ptr, train->col, train->val, b.hmap, thead, tnrm, ttcnt,
@@ -1319,8 +1292,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
         HIP_TRY(launch_ht_split(nq, H, queries->row_ptr, queries->col, queries->val, b.hmap, qhead, qnrm, qtcnt,
                                 (unsigned*)(b.misc + 3), s));
         uint32_t mb = 0;
-        HIP_TRY(hipMemcpyAsync(&mb, b.misc + 3, sizeof(mb), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(hipMemcpyAsync(&mb, b.misc + 3, sizeof(mb), hipMemcpyDeviceToHost, s));   // (waited for below)
         int rows_t = 0;
         if ((rc = ht_tile_rows(nq, nullptr, qtcnt, b.misc, s, &rows_t))) return rc;
         if (rows_t) {

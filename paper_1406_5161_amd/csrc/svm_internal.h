@@ -274,10 +274,9 @@ int device_cu_count();
 constexpr int HT_BLOCK = 512;         // threads per workgroup
 constexpr int HT_CHUNK = 64;          // support vectors per sweep step
 constexpr int HT_TILE_MAX = 64;       // target rows per workgroup (16, 32 or 64)
-constexpr int HT_ENTRIES = 4096;      // tail nonzeros of one tile of target rows (LDS table)
-constexpr int HT_SLOTS = 8192;        // LDS hash slots for their columns
-constexpr int HT_MAX_D = 65535;       // column ids fit the hash key
-constexpr int HT_MAX_WORDS = (HT_MAX_D + 32) / 32;   // head-column bitmap words
+constexpr int HT_ENTRIES = 5632;      // tail nonzeros of one tile of target rows (LDS table)
+constexpr int HT_MAX_D = 65535;
+constexpr int HT_MAX_WORDS = (HT_MAX_D + 32) / 32;   // words of a column bitmap
 constexpr int HT_H_MAX = 128;         // head columns: 32, 64 or 128
 constexpr int HT_H_DEFAULT = 128;
 
@@ -306,7 +305,8 @@ struct HtArgs {
     float* kout;
     int64_t ldk;
 };
-hipError_t launch_col_count(int64_t nnz, const int32_t* col, int32_t* cnt, hipStream_t s);
+hipError_t launch_col_count(int64_t nnz, int d, const int32_t* col, int32_t* cnt, hipStream_t s);
+hipError_t launch_ht_choose(int d, int H, const int32_t* cnt, int32_t* hmap, uint32_t* hbits, hipStream_t s);
 hipError_t launch_ht_split(int n, int H, const int32_t* rp, const int32_t* col, const float* val,
                            const int32_t* hmap, float* head, float* nrm, int32_t* tcnt, unsigned* maxn2,
                            hipStream_t s);
