@@ -51,7 +51,6 @@ unsigned long long*& prof_cfg() {
     return p;
 }
 
-constexpr int NSPLIT_MAX = 16;
 constexpr size_t ALIGN = 256;
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) & ~(ALIGN - 1); }
@@ -59,7 +58,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) & ~(ALIGN - 1); }
 struct Plan {
     size_t ctl, xpack, bits, fint, status, mask, act, seg, cnt, rec, listw, listz, coef, blkcnt, counts, part,
         sumblk, out6, work, htcnt, hthmap, htbits, hthead, htnrm, httcnt, htmisc, htbhead, htbnrm, httoff, httent,
-        kcache, ktags, col16, val2, prp, dbg, total;
+        kcache, ktags, col16, val2, prp, dbg, nrm, total;
     int64_t cache_rows;   // slots of the kernel-row cache (0: none)
     int tag_grid;         // workgroups the cache tags are sized for
 };
@@ -156,6 +155,7 @@ Plan make_plan(const svm_problem_t* p, const svm_params_t* params, int64_t nnz) 
     q.val2 = take(sizeof(float) * npad);
     q.prp = take(p->layout == SVM_CSR ? sizeof(int32_t) * (n + 1) : 0);
     q.dbg = take(sizeof(RegDebug));
+    q.nrm = take(p->layout == SVM_CSR ? 0 : sizeof(float) * n);
     q.total = o;
     return q;
 }
@@ -203,6 +203,19 @@ int ht_nsplit(int na, int rows, int nb) {
     long long cost = 0;
     for (int ns = 1; ns <= std::min<long long>(NSPLIT_MAX, std::max<long long>(1, chunks)); ++ns) {
         const long long c = ((blocks * ns + cus - 1) / cus) * ((chunks + ns - 1) / ns + 3);
+        if (ns == 1 || c < cost) { cost = c; best = ns; }
+    }
+    return best;
+}
+
+// Splits of the dense matrix-core sum, four workgroups a CU: the number for which the last round of them
+// ends first (a workgroup's start and end cost about two chunks).
+int dense_nsplit(long long blocks, long long nb, int most) {
+    const long long chunks = std::max<long long>(1, (nb + 63) / 64), slots = 4ll * std::max(1, device_cu_count());
+    int best = 1;
+    long long cost = 0;
+    for (int ns = 1; ns <= std::min<long long>(most, chunks); ++ns) {
+        const long long c = ((blocks * ns + slots - 1) / slots) * ((chunks + ns - 1) / ns + 2);
         if (ns == 1 || c < cost) { cost = c; best = ns; }
     }
     return best;
@@ -279,6 +292,8 @@ struct Solver {
     uint32_t* col2 = nullptr;   // CSR rows as element pairs (LAY_CSR_TABLE / LAY_CSR_SLOT)
     float* val2 = nullptr;
     int32_t* prp = nullptr;     // first pair of each row
+    float* nrm = nullptr;       // dense rows' |x|^2, formed for the first kernel sum
+    bool nrm_done = false;
     HtBufs ht{};                // wide CSR: dense head rows for the kernel sums
     int ht_H = 0;               // head columns in use (0: sparse kernel sums only)
     double t_start = 0;         // host clock at the start of the call
@@ -449,6 +464,12 @@ struct Solver {
             a.wpr = bits_wpr(d);
             a.rows_per_block = 16;
             blocks = (nrows + 15) / 16;
+        } else if (kernel_sum_uses_norms(a.lay, dpad, q->kernel_precision)) {
+            if (!nrm_done) HIP_TRY(launch_dense_norms(n, xin, nrm, 0, nullptr, nullptr, dpad, s));
+            nrm_done = true;
+            a.anrm = a.bnrm = nrm;
+            a.rows_per_block = KSUM_DENSE_ROWS;
+            blocks = (nrows + a.rows_per_block - 1) / a.rows_per_block;
         } else if (kernel_sum_uses_mfma(a.lay, dpad, q->kernel_precision)) {
             a.rows_per_block = KSUM_MFMA_ROWS;
             blocks = (nrows + KSUM_MFMA_ROWS - 1) / KSUM_MFMA_ROWS;
@@ -464,6 +485,7 @@ struct Solver {
         }
         int ns = std::max(1, std::min(NSPLIT_MAX, (2048 + blocks - 1) / blocks));
         ns = std::min(ns, std::max(1, nz / 256));
+        if (a.anrm) ns = dense_nsplit(blocks, nz, NSPLIT_MAX);
         a.nsplit = ns;
         a.part = part;
         HIP_TRY(hipEventRecord(ev2, s));
@@ -727,6 +749,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
         float* xp = S.at<float>(S.plan.xpack);
         HIP_TRY(launch_pack_dense(p->n, p->d, S.dpad, p->x, p->ldx, p->layout == SVM_DENSE_FEATURE_MAJOR, xp, s));
         S.xin = xp;
+        S.nrm = S.at<float>(S.plan.nrm);
     }
 
     // ---- grid size and residency: co-resident workgroups (cooperative launch), each owning a
@@ -1236,16 +1259,23 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     const ValPart valt = val_sum(hvt, n), valq = val_sum(hvq, nq);
     if ((valt.flags | valq.flags) & VAL_MALFORMED) return SVM_EINVAL;
     if ((valt.flags | valq.flags) & VAL_NONFINITE) return SVM_ENONFINITE;
+    // support vectors: ascending ids with alpha > 0, coefficient alpha * y
+    HIP_TRY(launch_compact(n, 1, nullptr, alpha, train->y, bc, lz, cf, ct, s));
+    // dense FP32 rows for the matrix cores: the support vectors' rows alone, in that order; once they
+    // are packed their norms take the place of the ids, and the queries' norms that of the last split's
+    // partial sums
+    const bool norms = kernel_sum_uses_norms(dense ? LAY_DENSE : LAY_CSR_TABLE, dpad, kprec);
+    float* qn = (float*)(pt + (size_t)(NSPLIT_MAX - 1) * nq);
     if (dense) {
-        HIP_TRY(launch_pack_dense(n, d, dpad, train->x, train->ldx, train->layout == SVM_DENSE_FEATURE_MAJOR, xt, s));
+        HIP_TRY(launch_pack_dense(n, d, dpad, train->x, train->ldx, train->layout == SVM_DENSE_FEATURE_MAJOR, xt, s,
+                                  norms ? lz : nullptr, ct));
         HIP_TRY(launch_pack_dense(nq, d, dpad, queries->x, queries->ldx, queries->layout == SVM_DENSE_FEATURE_MAJOR,
                                   xq, s));
     }
-    // support vectors: ascending ids with alpha > 0, coefficient alpha * y
-    HIP_TRY(launch_compact(n, 1, nullptr, alpha, train->y, bc, lz, cf, ct, s));
     int32_t nz = 0;
     HIP_TRY(hipMemcpyAsync(&nz, ct, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (norms) HIP_TRY(launch_dense_norms(nz, xt, (float*)lz, nq, xq, qn, dpad, s));
 
     SumArgs a{};
     a.lay = dense ? LAY_DENSE : LAY_CSR_TABLE;
@@ -1321,7 +1351,13 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     if (a.lay != LAY_BITS) {
         const int W = dense ? dpad : d;
         const int R = (int)std::min<size_t>(16, (96 * 1024) / (sizeof(float) * (size_t)W));
-        if (kernel_sum_uses_mfma(a.lay, dpad, kprec)) {
+        if (norms) {
+            a.blist = nullptr;
+            a.anrm = qn;
+            a.bnrm = (const float*)lz;
+            a.rows_per_block = KSUM_DENSE_ROWS;
+            blocks = (nq + a.rows_per_block - 1) / a.rows_per_block;
+        } else if (kernel_sum_uses_mfma(a.lay, dpad, kprec)) {
             a.rows_per_block = KSUM_MFMA_ROWS;
             blocks = (nq + KSUM_MFMA_ROWS - 1) / KSUM_MFMA_ROWS;
         } else if (R < 1) {
@@ -1340,6 +1376,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     }
     int ns = std::max(1, std::min(NSPLIT_MAX, (2048 + blocks - 1) / blocks));
     ns = std::min(ns, std::max(1, nz / 256));
+    if (norms) ns = dense_nsplit(blocks, nz, NSPLIT_MAX - 1);
     a.nsplit = ns;
     HIP_TRY(launch_kernel_sum(a, kprec, s));
     HIP_TRY(launch_finish_sum(nq, ns, pt, nullptr, nullptr, beta, out, s));

@@ -204,7 +204,12 @@ struct SumArgs {
     const uint32_t* bbits;
     int32_t wpr;
     int32_t slot_rows;        // LAY_CSR_SLOT: A rows per group (slot_rows_for)
+    // kernel_sum_uses_norms: |x|^2 of the A and B rows (indexed as ax and bx; blist may then be NULL:
+    // B rows 0 .. nb-1)
+    const float* anrm;
+    const float* bnrm;
 };
+constexpr int NSPLIT_MAX = 16;
 // A rows the wide-CSR kernel sum groups per pass for the longest row max_nnz and d columns:
 // the most (at most 8) whose column table fits the LDS next to the slot map.
 int slot_rows_for(int d, int max_nnz);
@@ -233,7 +238,7 @@ inline ValPart val_sum(const ValPart* part, int n) {
     return t;
 }
 hipError_t launch_pack_dense(int n, int d, int dpad, const float* x, int64_t ldx, int feature_major, float* out,
-                             hipStream_t s);
+                             hipStream_t s, const int32_t* list = nullptr, const int32_t* count = nullptr);
 hipError_t launch_init_state(int n, const int8_t* y, double C, int warm, double* alpha, double* f, uint8_t* status,
                              hipStream_t s);
 hipError_t launch_reset_active(int n, int G, int32_t* seg_start, int32_t* cnt, int32_t* act, hipStream_t s);
@@ -252,6 +257,10 @@ hipError_t launch_compact(int n, int pred, const uint8_t* mask, const double* al
                           int32_t* blk_cnt, int32_t* list, double* coef, int32_t* count_out, hipStream_t s);
 hipError_t launch_kernel_sum(const SumArgs& a, int kprec, hipStream_t s);
 bool kernel_sum_uses_mfma(int lay, int dpad, int kprec);   // dense FP32 sums on the matrix cores
+bool kernel_sum_uses_norms(int lay, int dpad, int kprec);  // of them, those that take the rows' norms
+constexpr int KSUM_DENSE_ROWS = 64;                        // A rows per workgroup of those
+hipError_t launch_dense_norms(int n1, const float* x1, float* o1, int n2, const float* x2, float* o2, int dpad,
+                              hipStream_t s);
 constexpr int KSUM_MFMA_ROWS = 64;                         // A rows per workgroup of that kernel
 // out[alist[r]] = sum_s part[s][r] + bias (bias: -y[alist[r]] if y != NULL, else -beta)
 hipError_t launch_finish_sum(int na, int nsplit, const double* part, const int32_t* alist, const int8_t* y,

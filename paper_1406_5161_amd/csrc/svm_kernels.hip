@@ -111,21 +111,26 @@ hipError_t launch_validate(int n, int d, int lay, const float* x, int64_t ldx, i
     return hipGetLastError();
 }
 
+// Rows to [n][dpad] (zeros beyond d).  With a list, row r of the output is sample list[r], for the first
+// *count of them (in device memory; n is the most there can be).
 __global__ void pack_dense_kernel(int n, int d, int dpad, const float* __restrict__ x, int64_t ldx, int feature_major,
-                                  float* __restrict__ out) {
+                                  float* __restrict__ out, const int32_t* __restrict__ list,
+                                  const int32_t* __restrict__ count) {
     const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (size_t)n * dpad) return;
-    const int i = (int)(e / dpad), k = (int)(e % dpad);
+    const int r = (int)(e / dpad), k = (int)(e % dpad);
+    if (list && r >= *count) return;
+    const int i = list ? list[r] : r;
     float v = 0.f;
     if (k < d) v = feature_major ? x[(size_t)k * ldx + i] : x[(size_t)i * ldx + k];
     out[e] = v;
 }
 
 hipError_t launch_pack_dense(int n, int d, int dpad, const float* x, int64_t ldx, int feature_major, float* out,
-                             hipStream_t s) {
+                             hipStream_t s, const int32_t* list, const int32_t* count) {
     size_t tot = (size_t)n * dpad;
     if (!tot) return hipSuccess;
-    pack_dense_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(n, d, dpad, x, ldx, feature_major, out);
+    pack_dense_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(n, d, dpad, x, ldx, feature_major, out, list, count);
     return hipGetLastError();
 }
 
@@ -599,15 +604,202 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_slot_kernel(SumArgs A) {
     }
 }
 
-// Dense rows, FP32 kernel values: the distance terms come from matrix-core products.  A
+// Dense rows of up to 128 features, FP32 kernel values, on the matrix cores.  A workgroup (4 waves)
+// takes 64 rows of A, 16 a wave, whose values stay in registers (K4 a lane and 16 rows), and
+// sweeps its split of the B rows 64 at a time: the chunk goes to LDS (double-buffered, loaded one
+// chunk ahead; [k / 4][row][4], so that a matrix operand is 64 consecutive words) with its norms and
+// coefficients, each wave forms 16 x 16 blocks of dot products by v_mfma_f32_16x16x4f32 and applies
+// d2 = |a|^2 + |b|^2 - 2 a.b (clamped at 0), exp(-gamma d2) and coef_b K into FP64 row sums.  Operand
+// lanes: A[row][k] and B[k][col] sit in lane (row or col) + 16 k; output C[row][col] in lane
+// col + 16 (row / 4), register row % 4.
+// The products need 32 K4 cycles of a matrix core per 256 pairs and the epilogue about 51 vector
+// instructions (280 cycles with the exponential and the conversions); the counters show the two adding up
+// rather than overlapping, so what helps is less of either: norms come from a pass of their own (in the
+// sweep they cost two barriers a chunk and 64 of 256 threads summing) and the rows' values from registers.
+// 10,000 x 95,000 pairs, d = 28: 0.77 ms, against 1.33 with both tiles in LDS and the norms in the
+// sweep; two 16-row blocks a wave, 0.85 (three waves a SIMD instead of five).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int MD_K4_MAX = 32;
+constexpr int MD_CHUNK = 64;
+
+template <int K4>
+__global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_dense_kernel(SumArgs A) {
+    constexpr int NV = (K4 * MD_CHUNK + SUM_BLOCK - 1) / SUM_BLOCK;   // float4 of a chunk per thread
+    __shared__ __align__(16) f32x4 s_b[2][K4][MD_CHUNK];
+    __shared__ float s_nb[2][MD_CHUNK];
+    __shared__ double s_cb[2][MD_CHUNK];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int m16 = lane & 15, mk = lane >> 4;
+    const int n4 = A.dpad >> 2;
+    const int r0 = blockIdx.x * KSUM_DENSE_ROWS + 16 * wid;   // the wave's first row
+    float ar[K4], na[4];
+    {
+        const int r = r0 + m16;
+        const float* src = r < A.na ? A.ax + (size_t)(A.alist ? A.alist[r] : r) * A.dpad : nullptr;
+#pragma unroll
+        for (int k = 0; k < K4; ++k) ar[k] = src && k < n4 ? src[4 * k + mk] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int q = r0 + 4 * mk + i;
+            na[i] = q < A.na ? A.anrm[A.alist ? A.alist[q] : q] : 0.f;
+        }
+    }
+    const float gam = (float)A.gamma;
+    // splits are whole chunks
+    const int per = (A.nb + A.nsplit * MD_CHUNK - 1) / (A.nsplit * MD_CHUNK) * MD_CHUNK;
+    const int b0 = min(A.nb, (int)blockIdx.y * per), b1 = min(A.nb, b0 + per);
+    f32x4 hv[NV];
+    float pn = 0.f;
+    double pc = 0.0;
+    auto load = [&](int c0) {   // chunk c0 into registers: lane l of a quad of waves takes row l
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int e = tid + SUM_BLOCK * v, k = e / MD_CHUNK, j = c0 + e % MD_CHUNK;
+            hv[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (k < n4 && j < b1)
+                hv[v] = reinterpret_cast<const f32x4*>(A.bx + (size_t)(A.blist ? A.blist[j] : j) * A.dpad)[k];
+        }
+        if (tid < MD_CHUNK) {
+            const int j = c0 + tid;
+            const bool in = j < b1;
+            pn = in ? A.bnrm[A.blist ? A.blist[j] : j] : 0.f;
+            pc = in ? A.coef[j] : 0.0;
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int e = tid + SUM_BLOCK * v, k = e / MD_CHUNK;
+            if (k < K4) s_b[buf][k][e % MD_CHUNK] = hv[v];
+        }
+        if (tid < MD_CHUNK) {
+            s_nb[buf][tid] = pn;
+            s_cb[buf][tid] = pc;
+        }
+    };
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (b0 < b1) {
+        load(b0);
+        store(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int c0 = b0; c0 < b1; c0 += MD_CHUNK, buf ^= 1) {
+        const bool more = c0 + MD_CHUNK < b1;
+        if (more) load(c0 + MD_CHUNK);
+        auto block = [&](int cb) {   // 16 rows by columns 16 cb .. of the chunk
+            f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < K4; ++k)
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    ar[k], reinterpret_cast<const float*>(&s_b[buf][k][16 * cb + m16])[mk], d, 0, 0, 0);
+            return d;
+        };
+        // a block's products run on the matrix core while the one before is reduced
+        f32x4 d = block(0);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const f32x4 cur = d;
+            if (cb < 3) d = block(cb + 1);
+            const float nbc = s_nb[buf][16 * cb + m16];
+            const double cbv = s_cb[buf][16 * cb + m16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d2 = na[i] + nbc - 2.f * cur[i];
+                d2 = d2 < 0.f ? 0.f : d2;
+                acc[i] += cbv * (double)kexp(-gam * d2);
+            }
+            if (cb < 3) {
+#pragma unroll
+                for (int k = 0; k < K4; ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x008 /* matrix */, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002 /* vector ALU */, (48 + K4 - 1) / K4, 0);
+                }
+            }
+        }
+        if (more) store(buf ^ 1);
+        __syncthreads();
+    }
+    // rows 4 mk + i of the wave: add the 16 lanes (columns) that share mk
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        double v = acc[i];
+        v = xor_add<1>(v);
+        v = xor_add<2>(v);
+        v = xor_add<4>(v);
+        v = xor_add<8>(v);
+        const int r = r0 + 4 * mk + i;
+        if (m16 == 0 && r < A.na) A.part[(size_t)blockIdx.y * A.na + r] = v;
+    }
+}
+
+// |x|^2 of packed dense rows in feature order (FP32): two sets in one launch (n2 may be 0).
+__global__ __launch_bounds__(256) void dense_norms_kernel(int n1, const float* __restrict__ x1, float* o1, int n2,
+                                                          const float* __restrict__ x2, float* o2, int dpad) {
+    int i = blockIdx.x * 256 + threadIdx.x;
+    const float* x = x1;
+    float* o = o1;
+    if (i >= n1) {
+        i -= n1;
+        if (i >= n2) return;
+        x = x2;
+        o = o2;
+    }
+    const float4* r = reinterpret_cast<const float4*>(x + (size_t)i * dpad);
+    float s = 0.f;
+    for (int k = 0; k < dpad / 4; ++k) {
+        const float4 v = r[k];
+        s = fmaf(v.x, v.x, s);
+        s = fmaf(v.y, v.y, s);
+        s = fmaf(v.z, v.z, s);
+        s = fmaf(v.w, v.w, s);
+    }
+    o[i] = s;
+}
+
+hipError_t launch_dense_norms(int n1, const float* x1, float* o1, int n2, const float* x2, float* o2, int dpad,
+                              hipStream_t s) {
+    const int64_t n = (int64_t)n1 + n2;
+    if (n <= 0) return hipSuccess;
+    dense_norms_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n1, x1, o1, n2, x2, o2, dpad);
+    return hipGetLastError();
+}
+
+// Row width (in float4) of the instance for rows of dpad floats; 0: none
+static int dense_sum_width(int dpad) {
+    static const int w[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32};
+    for (int k : w)
+        if (4 * k >= dpad) return k;
+    return 0;
+}
+static const void* dense_sum_pick(int k4) {
+    switch (k4) {
+        case 1: return (const void*)kernel_sum_dense_kernel<1>;
+        case 2: return (const void*)kernel_sum_dense_kernel<2>;
+        case 3: return (const void*)kernel_sum_dense_kernel<3>;
+        case 4: return (const void*)kernel_sum_dense_kernel<4>;
+        case 5: return (const void*)kernel_sum_dense_kernel<5>;
+        case 6: return (const void*)kernel_sum_dense_kernel<6>;
+        case 7: return (const void*)kernel_sum_dense_kernel<7>;
+        case 8: return (const void*)kernel_sum_dense_kernel<8>;
+        case 12: return (const void*)kernel_sum_dense_kernel<12>;
+        case 16: return (const void*)kernel_sum_dense_kernel<16>;
+        case 24: return (const void*)kernel_sum_dense_kernel<24>;
+        case 32: return (const void*)kernel_sum_dense_kernel<32>;
+        default: return nullptr;
+    }
+}
+
+bool kernel_sum_uses_norms(int lay, int dpad, int kprec) {
+    return lay == LAY_DENSE && kprec == SVM_KERNEL_FP32 && dpad <= 4 * MD_K4_MAX;
+}
+// Dense rows beyond that, FP32 kernel values: both sides' tiles in LDS.  A
 // workgroup (4 waves) holds 64 A rows in LDS and sweeps its split of the B list 64 rows at a
 // time; wave w forms the 16 x 64 block of dot products of A rows 16w.. with the chunk through
 // v_mfma_f32_16x16x4f32 (a 16x4 by 4x16 product per instruction, K = dpad in steps of 4), then
 // applies the epilogue d2 = |a|^2 + |b|^2 - 2 a.b (clamped at 0), exp(-gamma d2), and adds
-// coef_b * K into FP64 row sums.  Operand lanes: A[row][k] and B[k][col] sit in lane
-// (row or col) + 16 k; output C[row][col] in lane col + 16 (row / 4), register row % 4.
+// coef_b * K into FP64 row sums.
 constexpr int MF_T = 64;              // A rows per workgroup, B rows per chunk
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int MF_MAX_DPAD = 240;      // LDS: 2 x 64 rows x (dpad + 1) floats
 
 __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_mfma_kernel(SumArgs A) {
@@ -772,6 +964,14 @@ hipError_t launch_kernel_sum(const SumArgs& a, int kprec, hipStream_t s) {
         if (kprec == SVM_KERNEL_FP64) kernel_sum_bits_kernel<double><<<grid, SUM_BLOCK, lds, s>>>(c);
         else kernel_sum_bits_kernel<float><<<grid, SUM_BLOCK, lds, s>>>(c);
         return hipGetLastError();
+    }
+    if (kernel_sum_uses_norms(a.lay, a.dpad, kprec)) {
+        const void* fn = dense_sum_pick(dense_sum_width(a.dpad));
+        if (!fn || !a.anrm || !a.bnrm) return hipErrorInvalidValue;
+        SumArgs c = a;
+        void* args[] = {&c};
+        return hipLaunchKernel(fn, dim3((a.na + a.rows_per_block - 1) / a.rows_per_block, a.nsplit), dim3(SUM_BLOCK),
+                               args, 0, s);
     }
     if (kernel_sum_uses_mfma(a.lay, a.dpad, kprec)) {
         const size_t lds = sizeof(float) * 2 * MF_T * (size_t)(a.dpad + 1);
