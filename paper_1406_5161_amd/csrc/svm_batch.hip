@@ -1272,23 +1272,31 @@ __global__ __launch_bounds__(BB) void smo_batch_kernel(BatchArgs A) {
     }
 }
 
-// Bitset rows from CSR columns (one thread per row; columns increasing, as validated).
-__global__ void pack_bits_kernel(int n, int d, int wpr, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                 uint32_t* __restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint32_t* o = out + (size_t)i * wpr;
-    for (int k = 0; k < wpr; ++k) o[k] = 0u;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) {
-        const int c = col[p];
-        if (c >= 0 && c < d) o[c >> 5] |= 1u << (c & 31);
+// Bitset rows from CSR columns: 16 lanes a row set its bits in LDS, and the words leave in one piece.
+constexpr int PACK_ROWS = 16;
+__global__ __launch_bounds__(256) void pack_bits_kernel(int n, int d, int wpr, const int32_t* __restrict__ rp,
+                                                        const int32_t* __restrict__ col, uint32_t* __restrict__ out) {
+    __shared__ uint32_t s_w[PACK_ROWS * (BITS_MAX_D / 32)];
+    const int r0 = blockIdx.x * PACK_ROWS, nr = min(PACK_ROWS, n - r0);
+    const int tid = threadIdx.x, r = tid >> 4;
+    for (int k = tid; k < PACK_ROWS * wpr; k += 256) s_w[k] = 0u;
+    __syncthreads();
+    if (r < nr) {
+        const int p1 = rp[r0 + r + 1];
+        for (int p = rp[r0 + r] + (tid & 15); p < p1; p += 16) {
+            const int c = col[p];
+            if (c >= 0 && c < d) atomicOr(&s_w[r * wpr + (c >> 5)], 1u << (c & 31));
+        }
     }
+    __syncthreads();
+    for (int k = tid; k < nr * wpr; k += 256) out[(size_t)r0 * wpr + k] = s_w[k];
 }
 
 hipError_t launch_pack_bits(int n, int d, int wpr, const int32_t* row_ptr, const int32_t* col, uint32_t* out,
                             hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    pack_bits_kernel<<<(n + 255) / 256, 256, 0, s>>>(n, d, wpr, row_ptr, col, out);
+    if (wpr < 1 || wpr > BITS_MAX_D / 32) return hipErrorInvalidValue;
+    pack_bits_kernel<<<(n + PACK_ROWS - 1) / PACK_ROWS, 256, 0, s>>>(n, d, wpr, row_ptr, col, out);
     return hipGetLastError();
 }
 

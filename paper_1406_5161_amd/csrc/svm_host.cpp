@@ -208,7 +208,7 @@ int ht_nsplit(int na, int rows, int nb) {
     return best;
 }
 
-// Splits of the dense matrix-core sum, four workgroups a CU: the number for which the last round of them
+// Splits of the dense and bitset matrix-core sums, about four workgroups a CU: the number for which the last round of them
 // ends first (a workgroup's start and end cost about two chunks).
 int dense_nsplit(long long blocks, long long nb, int most) {
     const long long chunks = std::max<long long>(1, (nb + 63) / 64), slots = 4ll * std::max(1, device_cu_count());
@@ -462,8 +462,8 @@ struct Solver {
             a.lay = LAY_BITS;
             a.abits = a.bbits = bits;
             a.wpr = bits_wpr(d);
-            a.rows_per_block = 16;
-            blocks = (nrows + 15) / 16;
+            a.rows_per_block = kernel_sum_bits_rows(d);
+            blocks = (nrows + a.rows_per_block - 1) / a.rows_per_block;
         } else if (kernel_sum_uses_norms(a.lay, dpad, q->kernel_precision)) {
             if (!nrm_done) HIP_TRY(launch_dense_norms(n, xin, nrm, 0, nullptr, nullptr, dpad, s));
             nrm_done = true;
@@ -485,7 +485,7 @@ struct Solver {
         }
         int ns = std::max(1, std::min(NSPLIT_MAX, (2048 + blocks - 1) / blocks));
         ns = std::min(ns, std::max(1, nz / 256));
-        if (a.anrm) ns = dense_nsplit(blocks, nz, NSPLIT_MAX);
+        if (a.anrm || a.lay == LAY_BITS) ns = dense_nsplit(blocks, nz, NSPLIT_MAX);
         a.nsplit = ns;
         a.part = part;
         HIP_TRY(hipEventRecord(ev2, s));
@@ -1296,8 +1296,8 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
             a.bbits = (uint32_t*)(ws + P.tbits);
             HIP_TRY(launch_pack_bits(nq, d, a.wpr, queries->row_ptr, queries->col, (uint32_t*)a.abits, s));
             HIP_TRY(launch_pack_bits(n, d, a.wpr, train->row_ptr, train->col, (uint32_t*)a.bbits, s));
-            a.rows_per_block = 16;
-            blocks = (nq + 15) / 16;
+            a.rows_per_block = kernel_sum_bits_rows(d);
+            blocks = (nq + a.rows_per_block - 1) / a.rows_per_block;
         }
     }
     if (!dense && a.lay != LAY_BITS && ht_capable(train) && kprec == SVM_KERNEL_FP32) {
@@ -1376,7 +1376,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     }
     int ns = std::max(1, std::min(NSPLIT_MAX, (2048 + blocks - 1) / blocks));
     ns = std::min(ns, std::max(1, nz / 256));
-    if (norms) ns = dense_nsplit(blocks, nz, NSPLIT_MAX - 1);
+    if (norms || a.lay == LAY_BITS) ns = dense_nsplit(blocks, nz, norms ? NSPLIT_MAX - 1 : NSPLIT_MAX);
     a.nsplit = ns;
     HIP_TRY(launch_kernel_sum(a, kprec, s));
     HIP_TRY(launch_finish_sum(nq, ns, pt, nullptr, nullptr, beta, out, s));

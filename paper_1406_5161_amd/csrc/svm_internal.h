@@ -258,6 +258,7 @@ hipError_t launch_compact(int n, int pred, const uint8_t* mask, const double* al
 hipError_t launch_kernel_sum(const SumArgs& a, int kprec, hipStream_t s);
 bool kernel_sum_uses_mfma(int lay, int dpad, int kprec);   // dense FP32 sums on the matrix cores
 bool kernel_sum_uses_norms(int lay, int dpad, int kprec);  // of them, those that take the rows' norms
+int kernel_sum_bits_rows(int d);                           // A rows per workgroup of the bitset sums
 constexpr int KSUM_DENSE_ROWS = 64;                        // A rows per workgroup of those
 hipError_t launch_dense_norms(int n1, const float* x1, float* o1, int n2, const float* x2, float* o2, int dpad,
                               hipStream_t s);
