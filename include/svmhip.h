@@ -223,12 +223,14 @@ int svm_decision_noalloc(const svm_problem_t* train, const double* alpha, double
  * when that share is at least 512 samples; else about 1500 samples per
  * workgroup, whose rows stream from HBM while their f, status and active
  * list stay in LDS; a team size recorded by svm_autotune for the problem's class
- * replaces that rule, and params[p].grid_blocks overrides both), problems never synchronise
+ * replaces that rule, and params[p].grid_blocks overrides both); workgroups of the
+ * launch that these teams would leave idle join the problems with the most rows to
+ * stream, as far as they are free when the problem starts; problems never synchronise
  * with each other.  Every problem runs the whole method of svm_train (SMO
  * loop, shrinking, reconstruction, closing recompute) inside its team; alpha
  * and f do not depend on the team size or on the other problems.  alpha[p]
  * (device, n_p doubles) and f[p] (device or NULL) receive the solution; out[p]
- * (host) the result (grid_blocks = team size, ms_step = device time of the
+ * (host) the result (grid_blocks = the team's size, ms_step = device time of the
  * solve).  All problems share one kernel precision.  CSR rows may hold at
  * most 4096 nonzeros and d (dense: d rounded up to 4) at most about 1700
  * (SVM_EUNSUPPORTED beyond).  Lanes per row come from a built-in rule unless

@@ -277,6 +277,34 @@ DEV void select_block(const BatchDesc& P, const int32_t* act, int nact, BatchSha
 constexpr unsigned long long TEAM_GATHER_TICKS = 120ull * 100 * 1000 * 1000;
 constexpr unsigned long long TEAM_WAIT_TICKS = 30ull * 100 * 1000 * 1000;
 
+// A fixed batch asks for larger teams than it needs where workgroups would stand idle.  On a GPU
+// that other work holds in part they may not come: a team that has its least size waits this long
+// for the rest (a launch on a free GPU has all of its workgroups running well within it).
+constexpr unsigned long long TEAM_JOIN_TICKS = 20000;
+
+// Rank of the calling thread's workgroup in the team of problem `slot`, and the team's size, fixed
+// by its first member; -1 if the team started without it.  One thread of the workgroup calls it.
+DEV int team_join(int32_t* join, int want, int least, int& size) {
+    constexpr int CLOSED = 1 << 30;
+    const int r = __hip_atomic_fetch_add(join, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (r & CLOSED) return -1;
+    if (r == 0) {
+        const unsigned long long t0 = wall_clock64();
+        for (;;) {
+            const int c = __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long t = wall_clock64() - t0;
+            if (c >= want || (c >= least && t > TEAM_JOIN_TICKS) || t > TEAM_GATHER_TICKS) break;
+            __builtin_amdgcn_s_sleep(4);
+        }
+        size = __hip_atomic_fetch_or(join, CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(join + 1, size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        while (!(size = __hip_atomic_load(join + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+            __builtin_amdgcn_s_sleep(4);
+    }
+    return r;
+}
+
 struct TeamSel {
     double bu, bl, au, al;
     int iu, il;
@@ -1054,17 +1082,22 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
         ++n_recon;
     }
     lap(4);
-    // ---- threshold and summary over the team
+    // ---- threshold and summary: rank 0 sums over all rows, so that these too do not depend on the
+    // team's size, which in a batch follows from the workgroups that were free
     if (res) to_global();
-    double x6[6] = {0, 0, 0, 0, 0, 0}, s6[6];
+    double s6[6] = {0, 0, 0, 0, 0, 0};
     if (alive) {
+        double z6[6];
+        if (!team_sum(P, rank, seq++, s6, z6, true, sh)) alive = false;   // publishes alpha and f
+    }
+    if (alive && rank == 0) {
         double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0;
-        for (int i = seg0 + tid; i < seg1; i += BB) {
-            const double a = ld_agent(P.alpha + i);
+        for (int i = tid; i < n; i += BB) {
+            const double a = ld_agent(P.alpha + i), fi = ld_agent(P.f + i);
             const double yi = P.y[i] > 0 ? 1.0 : -1.0;
-            if (a > 0.0 && a < C) { v0 += P.f[i]; v1 += 1.0; }
+            if (a > 0.0 && a < C) { v0 += fi; v1 += 1.0; }
             v2 += a;
-            v3 += a * yi * (P.f[i] + yi);
+            v3 += a * yi * (fi + yi);
             if (a > 0.0) v4 += 1.0;
             if (a >= C) v5 += 1.0;
         }
@@ -1077,9 +1110,8 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
         __syncthreads();
         if (tid < 64)
             for (int w = 0; w < BNW; ++w)
-                for (int k = 0; k < 6; ++k) x6[k] += sh.red[w][k];
+                for (int k = 0; k < 6; ++k) s6[k] += sh.red[w][k];
         __syncthreads();
-        if (!team_sum(P, rank, seq++, x6, s6, true, sh)) alive = false;
     }
     // ---- completion: every member posts an acknowledgement and leaves; rank 0 waits for all of
     // them before it publishes the result (after which the host may reuse the team records)
@@ -1120,6 +1152,7 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
         __hip_atomic_store(&R->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&R->shrink_passes, passes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&R->shrunk_total, shrunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&R->team, P.team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&R->t_start, t_start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&R->t_end, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&R->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1259,13 +1292,16 @@ __global__ __launch_bounds__(BB) void smo_batch_kernel(BatchArgs A) {
             sh.ticket = ok ? t : -1;
             if (ok) {
                 const int2 tk = A.tickets[t & (A.tcapacity - 1)];
+                const int slot = tk.x & (A.capacity - 1);
                 sh.rank = tk.y;
-                sh.P = A.descs[tk.x & (A.capacity - 1)];
+                sh.P = A.descs[slot];
+                if (A.join) sh.rank = team_join(A.join + 2 * slot, sh.P.team, sh.P.team_min, sh.P.team);
             }
         }
         __syncthreads();
         if (sh.ticket < 0) break;
-        if (sh.rank < 0) prep_job(sh);
+        if (sh.rank < 0 && A.join) __syncthreads();       // the team started without this workgroup
+        else if (sh.rank < 0) prep_job(sh);
         else if (sh.P.lay == LAY_DENSE) solve_team<KT, LAY_DENSE>(sh, dyn);
         else if (sh.P.lay == LAY_BITS) solve_team<KT, LAY_BITS>(sh, dyn);
         else solve_team<KT, LAY_CSR_TABLE>(sh, dyn);

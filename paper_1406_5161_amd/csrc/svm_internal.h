@@ -402,6 +402,8 @@ struct BatchResult {
     unsigned long long t_start, t_end;   // device wall clock (100 MHz) around the solve
     int32_t done;                        // set last (release) when the fields above are final
     int32_t started;                     // set once the whole team has taken its tickets
+    int32_t team;                        // workgroups that solved the problem
+    int32_t pad;
 };
 
 // Outcome of a preparation job (validation, counts, dense packing) run by the serving loop.
@@ -428,7 +430,7 @@ struct BatchDesc {
     uint32_t flags;
     int32_t pad;
     int32_t team;                        // workgroups solving this problem together
-    int32_t pad2;
+    int32_t team_min;                    // BatchArgs::join: the team starts with this many if no more are free
     unsigned long long* trec;            // team exchange records [2][team][16], zeroed before the start
     unsigned long long* prof;            // NULL, or 8 device counters rank 0 adds its phase ticks to
     // preparation jobs only (ticket rank -1): the caller's samples, validated and, for dense
@@ -460,6 +462,8 @@ struct BatchArgs {
     int32_t* mirror;                     // device [2]: tail and shutdown as last seen by the leader
     int32_t fixed_tail;                  // > 0: a fixed batch (tail is this value, no polling)
     int32_t pad;
+    int32_t* join;                       // fixed batch: per problem the workgroups that came and, once
+                                         // fixed, the team's size (both zeroed); NULL when serving
 };
 
 hipError_t launch_batch(const BatchArgs& a, int workgroups, int kprec, hipStream_t s);

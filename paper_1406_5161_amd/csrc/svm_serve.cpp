@@ -30,6 +30,7 @@
 #include <deque>
 #include <map>
 #include <mutex>
+#include <queue>
 #include <thread>
 #include <vector>
 
@@ -150,6 +151,52 @@ int team_size(const svm_problem_t* p, const Inspect& in, int workers, int reques
         if (b <= cap) return std::max(1, b);
     }
     return std::max(1, std::min(cap, (p->n + 1499) / 1500));
+}
+
+// Give the workgroups that the teams of a batch leave idle to the problems with the most to gain.  An
+// iteration costs about 6 us whatever the team (pair staging, reductions, the exchange: 2.4 us from two
+// members up, 3.1 with 64) and `row` us per row a member holds; a solve takes of the order of n
+// iterations, but from a tenth of that to twice it, so each next member goes where n times the rows'
+// part is largest (24 problems of 1000 to 8000 samples: 59.7 ms; by the whole expected time, 63.9; without this rule, 147.1).  Measured for one problem alone, least team -> 32 members: 128 dense columns, n = 7308,
+// 136.8 -> 43.9 ms; 300-bit rows, n = 8000, 79.7 -> 54.1 ms; 20 columns, n = 6677, 5.5 -> 4.7 ms.
+// Below 0.5 us of rows a member a larger team gains nothing (the same three at 64: 38.6, 55.9, 4.7),
+// and a second member pays for its exchange from 4 us of rows on (20 columns, n = 1312, 3.5 us:
+// 5.3 ms alone, 5.6 with two).  The first sizes stay the least that a team may start with.
+void spread_teams(int k, const svm_problem_t* probs, const svm_params_t* params, const Inspect* ins, int workers,
+                  std::vector<int>& team) {
+    int64_t spare = workers;
+    for (const int t : team) spare -= t;
+    if (spare <= 0) return;
+    struct Cand {
+        double time;
+        int p;
+        bool operator<(const Cand& o) const { return time != o.time ? time < o.time : p > o.p; }
+    };
+    std::vector<double> rows(k);     // us an iteration with all rows in one member
+    std::priority_queue<Cand> q;
+    auto push = [&](int p) {
+        const double n = probs[p].n, t = rows[p] / team[p];
+        if (team[p] < TEAM_MAX && t >= 0.5 && (team[p] > 1 || t >= 4.0)) q.push(Cand{n * t, p});
+    };
+    for (int p = 0; p < k; ++p) {
+        if (params[p].grid_blocks > 0) continue;
+        const svm_problem_t& b = probs[p];
+        const int lay = batch_layout(&b, ins[p].pattern != 0);
+        if (tuned_shape(TuneClass{TUNE_TEAM, lay, params[p].kernel_precision, ins[p].pattern != 0,
+                                  params[p].shrink_mode != SVM_SHRINK_NONE, b.n, b.d}))
+            continue;
+        const double row = lay == LAY_DENSE ? 1.2e-3 + 7.5e-5 * dpad4(b.d)
+                           : lay == LAY_BITS ? 4e-4 + 1e-4 * bits_wpr(b.d)
+                                             : 1e-3 + 1.5e-4 * (double)ins[p].nnz / b.n;
+        rows[p] = row * b.n * (params[p].kernel_precision == SVM_KERNEL_FP64 && lay != LAY_BITS ? 2.0 : 1.0);
+        push(p);
+    }
+    for (; spare > 0 && !q.empty(); --spare) {
+        const int p = q.top().p;
+        q.pop();
+        ++team[p];
+        push(p);
+    }
 }
 
 int64_t shrink_h(const svm_params_t* q, int n) {
@@ -601,25 +648,38 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     }
     // one buffer for every problem's solver state, descriptors and results
     const int wg = std::max(1, batch_max_workgroups(kprec));
-    std::vector<int> team(k);
+    std::vector<int> team(k), least;
     std::vector<Inspect> ins(k);
-    int64_t nt = 0;
     if (const int rc = inspect(k, probs, s, ins.data())) return rc;
     for (int p = 0; p < k; ++p) {
         team[p] = team_size(&probs[p], ins[p], wg, params[p].grid_blocks, params[p].kernel_precision,
                             params[p].shrink_mode != SVM_SHRINK_NONE);
-        nt += team[p];
     }
+    least = team;
+    spread_teams(k, probs, params, ins.data(), wg, team);
     std::vector<size_t> off(k);
-    size_t o = al(sizeof(BatchDesc) * k) + al(sizeof(BatchResult) * k) + al(sizeof(Ctl) + 256) + al(64) +
-               al(sizeof(int2) * nt);
-    for (int p = 0; p < k; ++p) {
-        off[p] = o;
-        const ProbBytes b = prob_bytes(&probs[p], !(f && f[p]), team[p], team[p]);
-        o += b.base + b.team;
-    }
+    size_t o = 0, jo = 0;
+    int64_t nt = 0;
+    auto lay_out = [&]() {
+        nt = 0;
+        for (int p = 0; p < k; ++p) nt += team[p];
+        jo = al(sizeof(BatchDesc) * k) + al(sizeof(BatchResult) * k) + al(sizeof(Ctl) + 256) + al(64) +
+             al(sizeof(int2) * nt);
+        o = jo + al(sizeof(int32_t) * 2 * k);
+        for (int p = 0; p < k; ++p) {
+            off[p] = o;
+            const ProbBytes b = prob_bytes(&probs[p], !(f && f[p]), team[p], team[p]);
+            o += b.base + b.team;
+        }
+    };
     unsigned char* buf = nullptr;
-    if (hipMalloc(&buf, o) != hipSuccess) return SVM_ENOMEM;
+    lay_out();
+    if (hipMalloc(&buf, o) != hipSuccess) {
+        (void)hipGetLastError();
+        team = least;                       // each member holds 12 bytes a sample of its problem
+        lay_out();
+        if (hipMalloc(&buf, o) != hipSuccess) return SVM_ENOMEM;
+    }
     BatchDesc* ddesc = reinterpret_cast<BatchDesc*>(buf);
     BatchResult* dres = reinterpret_cast<BatchResult*>(buf + al(sizeof(BatchDesc) * k));
     int32_t* head = reinterpret_cast<int32_t*>(buf + al(sizeof(BatchDesc) * k) + al(sizeof(BatchResult) * k) +
@@ -629,8 +689,9 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     std::vector<BatchDesc> hd(k);
     int rc = SVM_OK;
     for (int p = 0; p < k && rc == SVM_OK; ++p)
-        rc = prepare(&probs[p], &params[p], ins[p], team[p], alpha[p], f ? f[p] : nullptr, buf + off[p], dres + p, s,
-                     &hd[p]);
+        if ((rc = prepare(&probs[p], &params[p], ins[p], team[p], alpha[p], f ? f[p] : nullptr, buf + off[p], dres + p,
+                          s, &hd[p])) == SVM_OK)
+            hd[p].team_min = least[p];
     if (rc) {
         (void)hipStreamSynchronize(s);
         (void)hipFree(buf);
@@ -658,6 +719,7 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     if (e == hipSuccess) e = hipMemcpyAsync(dtk, tk.data(), sizeof(int2) * nt, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemsetAsync(dres, 0, sizeof(BatchResult) * k, s);
     if (e == hipSuccess) e = hipMemsetAsync(head, 0, sizeof(int32_t), s);
+    if (e == hipSuccess) e = hipMemsetAsync(buf + jo, 0, sizeof(int32_t) * 2 * k, s);
     BatchArgs a{};
     a.descs = dring;
     a.capacity = cap;
@@ -668,6 +730,7 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     a.shutdown = head;
     a.mirror = head;
     a.fixed_tail = (int32_t)nt;
+    a.join = reinterpret_cast<int32_t*>(buf + jo);
     if (e == hipSuccess) e = launch_batch(a, (int)std::min<int64_t>(wg, nt), kprec, s);
     std::vector<BatchResult> hr(k);
     if (e == hipSuccess) e = hipMemcpyAsync(hr.data(), dres, sizeof(BatchResult) * k, hipMemcpyDeviceToHost, s);
@@ -676,7 +739,7 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
     if (e != hipSuccess) return SVM_EHIP;
     int worst = SVM_OK;
     for (int p = 0; p < k; ++p) {
-        fill_result(hr[p], team[p], &out[p]);
+        fill_result(hr[p], hr[p].team, &out[p]);
         if (hr[p].status != SVM_OK) worst = hr[p].status;
     }
     return worst;
