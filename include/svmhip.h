@@ -173,9 +173,10 @@ int svm_train(const svm_problem_t* prob, const svm_params_t* params, double* alp
 
 /* Several training problems over one sample set, trained in lockstep: one-vs-rest labelings
  * of a dataset or a C / gamma grid (the problems the paper's sample distribution shares, Sec.
- * "Data Structure Organization").  Each SMO iteration (Alg. 2, eq:fup, eq:bminmax) advances
- * every unconverged problem and reads each row once for all of them, so the row bytes per
- * problem-iteration fall about k-fold.  x: the shared samples (its y is not used); y[p]: the
+ * "Data Structure Organization").  Problems that fit the chip together with their rows in
+ * registers run side by side in one launch, each on its own workgroups.  Otherwise each SMO
+ * iteration (Alg. 2, eq:fup, eq:bminmax) advances every unconverged problem and reads each row
+ * once for all of them, so the row bytes per problem-iteration fall about k-fold.  x: the shared samples (its y is not used); y[p]: the
  * labels of problem p (device, n bytes); params[p]: its C, gamma, eps, max_iter and flags,
  * with shrink_mode SVM_SHRINK_NONE and one kernel_precision for all (SVM_EUNSUPPORTED
  * otherwise); alpha[p] / f[p] (f may be NULL) and out[p] as in svm_train.  1 <= k <= 8; rows

@@ -524,6 +524,20 @@ struct Solver {
         return SVM_OK;
     }
 
+    RegArgs reg_args(double thr, int64_t H) {
+        RegArgs r{};
+        r.stride = lay == LAY_BITS ? bits_wpr(d) : dpad;
+        r.x = xin; r.bits = bits;
+        r.y = p->y; r.alpha = alpha; r.f = f; r.status = status;
+        r.act = act; r.seg_start = seg; r.cnt = cnt;
+        r.rec = reinterpret_cast<unsigned long long*>(rec); r.ctl = ctl;
+        r.C = q->C; r.gamma = q->gamma; r.thr = thr;
+        r.max_iter = q->max_iter; r.H = H;
+        r.spin_limit = 500ull * 1000 * 1000;   // 5 s of the 100 MHz wall clock per record wait
+        r.work = work;
+        return r;
+    }
+
     int run_loop(double thr, int64_t H) {
         StepArgs a{};
         a.n = n; a.d = d; a.dpad = dpad; a.lay = lay;
@@ -559,14 +573,7 @@ struct Solver {
         a.epoch = ++epoch;   // tags of earlier launches (other active sets) never match
         RegArgs r{};
         if (reg_r) {
-            r.stride = lay == LAY_BITS ? a.wpr : dpad;
-            r.x = xin; r.bits = bits;
-            r.y = a.y; r.alpha = alpha; r.f = f; r.status = status;
-            r.act = act; r.seg_start = seg; r.cnt = cnt;
-            r.rec = reinterpret_cast<unsigned long long*>(rec); r.ctl = ctl;
-            r.C = a.C; r.gamma = a.gamma; r.thr = thr;
-            r.max_iter = a.max_iter; r.H = H;
-            r.spin_limit = a.spin_limit; r.work = work;
+            r = reg_args(thr, H);
             if (a.trace_cap || a.prof) {
                 const RegDebug d{a.trace_cap, a.tr_iu, a.tr_il, a.tr_bu, a.tr_bl, a.prof};
                 RegDebug* dd = at<RegDebug>(plan.dbg);
@@ -576,7 +583,7 @@ struct Solver {
             }
         }
         HIP_TRY(hipEventRecord(ev0, s));
-        if (reg_r) HIP_TRY(launch_reg(r, lay, q->kernel_precision == SVM_KERNEL_FP64, reg_w4, reg_r, G, s));
+        if (reg_r) HIP_TRY(launch_reg(&r, 1, lay, q->kernel_precision == SVM_KERNEL_FP64, reg_w4, reg_r, G, s));
         else HIP_TRY(launch_step(a, G, lpr, q->kernel_precision, plan_lds.total, s));
         HIP_TRY(hipEventRecord(ev1, s));
         int rc = read_ctl();
@@ -1004,6 +1011,29 @@ int shared_plan(const svm_problem_t* x, int k, const int8_t* const* y, const svm
     return SVM_OK;
 }
 
+// Workgroups of each problem where k problems fit the chip side by side with their rows in registers
+// (svm_regloop.h); 0: they do not.  The pass that serves all problems at once (svm_shared.hip) reads
+// the rows once instead of k times, but out of registers that saves nothing, it runs the problems'
+// pair updates, kernel values and reductions one behind the other, and its merge holds it to 64
+// workgroups: six problems of 20,000 300-bit rows take 14.4 us an iteration with it, 4.0 side by side
+// (40 workgroups each); four of 5000 rows of 20 columns 13.0 and 3.7.  The line is where the rows stop
+// fitting: then each row is read from LDS or memory, once for all.
+int shared_own_grid(const svm_problem_t* x, int k, const svm_params_t* params) {
+    const int lay = x->layout == SVM_CSR ? LAY_BITS : LAY_DENSE;
+    if (lay == LAY_BITS && x->d > BITS_MAX_D) return 0;
+    for (int p = 0; p < k; ++p)
+        if ((params[p].flags & (SVM_FLAG_NO_LDS_STATE | SVM_FLAG_NO_LDS_PAYLOAD | SVM_FLAG_NO_BITSETS)) ||
+            (lay == LAY_DENSE && cache_rows_for(x, &params[p])))
+            return 0;                        // asked for a form of the loop without them
+    const bool fp64 = params[0].kernel_precision == SVM_KERNEL_FP64;
+    const int w4 = reg_width(lay, lay == LAY_BITS ? bits_wpr(x->d) : dpad_of(x->d));
+    const int most = std::min(device_cu_count(), REG_GRID_MAX) / k;
+    if (!w4 || most < 1) return 0;
+    if ((int64_t)most * REG_BLOCK * reg_rows_max(fp64, w4) < x->n) return 0;
+    const int g = std::min(reg_grid_rule(fp64, w4, x->n, most), x->n);
+    return reg_rows(fp64, w4, (x->n + g - 1) / g) ? g : 0;
+}
+
 int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, const svm_params_t* params,
                       double* const* alpha, double* const* f, svm_result_t* out, unsigned char* ws, size_t ws_bytes,
                       hipStream_t s) {
@@ -1014,31 +1044,42 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
     if (rc) return rc;
     if (ws_bytes < P.total || ((uintptr_t)ws & (ALIGN - 1))) return SVM_EWORKSPACE;
     std::vector<svm_problem_t> probs(k, *x);
+    std::vector<svm_params_t> pars(params, params + k);
+    const int own = shared_own_grid(x, k, params);
     std::vector<std::unique_ptr<Solver>> sv;
     for (int p = 0; p < k; ++p) {
         if (!alpha || !alpha[p]) return SVM_EINVAL;
         probs[p].y = y[p];
+        if (own) pars[p].grid_blocks = own;
         sv.emplace_back(new Solver{});
-        if ((rc = prepare(*sv[p], &probs[p], &params[p], alpha[p], f ? f[p] : nullptr, ws + P.off[p], P.bytes[p], s)))
+        if ((rc = prepare(*sv[p], &probs[p], &pars[p], alpha[p], f ? f[p] : nullptr, ws + P.off[p], P.bytes[p], s)))
             return rc;
         // rows the shared pass handles: dense, or binary rows kept as bitsets
         if ((sv[p]->lay != LAY_DENSE && sv[p]->lay != LAY_BITS) || sv[p]->lay != sv[0]->lay) return SVM_EUNSUPPORTED;
     }
     const int lay = sv[0]->lay, kprec = params[0].kernel_precision;
     const int n = x->n, d = x->d;
-    // about 700 rows per workgroup (at most SHARED_GRID_MAX); each workgroup keeps its segment's
+    bool each = own > 0;              // every problem on workgroups of its own
+    for (int p = 0; p < k; ++p) each = each && sv[p]->reg_r && sv[p]->G == own;
+    each = each && reg_max_blocks(lay, kprec == SVM_KERNEL_FP64, sv[0]->reg_w4, sv[0]->reg_r) >= k * own;
+    // else one pass over the rows serves every problem: about 700 rows per workgroup (at most SHARED_GRID_MAX); each workgroup keeps its segment's
     // rows, f and status in LDS when they fit
     int G = std::max(1, std::min(SHARED_GRID_MAX, n <= 4096 ? 1 : (n + 350) / 700));
     int seg_max = (n + G - 1) / G;
-    const size_t lds_res = shared_lds_bytes(lay, d, seg_max, true);
-    bool res = lds_res <= STEP_LDS_BUDGET && shared_max_blocks(lay, kprec, true, lds_res) >= G;
-    size_t lds = shared_lds_bytes(lay, d, seg_max, res);
-    if (lds > STEP_LDS_BUDGET) return SVM_EUNSUPPORTED;
-    const int maxG = std::min(SHARED_GRID_MAX, shared_max_blocks(lay, kprec, res, lds));
-    if (maxG < 1) return SVM_EUNSUPPORTED;
-    if (G > maxG) {   // only without residency, whose LDS does not depend on the segment
-        G = maxG;
-        seg_max = (n + G - 1) / G;
+    bool res = false;
+    if (each) {
+        G = own;
+    } else {
+        const size_t lds_res = shared_lds_bytes(lay, d, seg_max, true);
+        res = lds_res <= STEP_LDS_BUDGET && shared_max_blocks(lay, kprec, true, lds_res) >= G;
+        size_t lds = shared_lds_bytes(lay, d, seg_max, res);
+        if (lds > STEP_LDS_BUDGET) return SVM_EUNSUPPORTED;
+        const int maxG = std::min(SHARED_GRID_MAX, shared_max_blocks(lay, kprec, res, lds));
+        if (maxG < 1) return SVM_EUNSUPPORTED;
+        if (G > maxG) {   // only without residency, whose LDS does not depend on the segment
+            G = maxG;
+            seg_max = (n + G - 1) / G;
+        }
     }
     Rec* rec = reinterpret_cast<Rec*>(ws + P.rec);
     unsigned long long* work = reinterpret_cast<unsigned long long*>(ws + P.work);
@@ -1046,34 +1087,53 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
     int running = (1 << k) - 1;
     hipEvent_t e0 = sv[0]->ev0, e1 = sv[0]->ev1;
     while (running) {
-        SharedArgs a{};
-        a.n = n; a.d = d; a.dpad = dpad_of(d); a.lay = lay;
-        a.wpr = lay == LAY_BITS ? bits_wpr(d) : 0;
-        a.k = k;
-        a.live_mask = running;
-        a.seg_max = seg_max;
-        a.res = res ? 1 : 0;
-        a.x = sv[0]->xin;
-        a.bits = sv[0]->bits;
-        a.rec = rec;
-        a.spin_limit = 500ull * 1000 * 1000;   // 5 s of the 100 MHz wall clock per record wait
-        a.work = work;
-        for (int p = 0; p < k; ++p) {
-            SharedProb& b = a.prob[p];
-            b.y = y[p]; b.alpha = alpha[p]; b.f = sv[p]->f; b.status = sv[p]->status; b.ctl = sv[p]->ctl;
-            b.C = params[p].C; b.gamma = params[p].gamma; b.thr = 2.0 * params[p].eps; b.max_iter = params[p].max_iter;
+        unsigned long long rows = 0;
+        if (each) {
+            std::vector<RegArgs> ra;
+            for (int p = 0; p < k; ++p) {
+                if (!((running >> p) & 1)) continue;
+                ra.push_back(sv[p]->reg_args(2.0 * params[p].eps, 0));
+                HIP_TRY(hipMemsetAsync(ra.back().rec, 0, sizeof(unsigned long long) * 2 * 8 * G, s));
+            }
+            HIP_TRY(hipEventRecord(e0, s));
+            HIP_TRY(launch_reg(ra.data(), (int)ra.size(), lay, kprec == SVM_KERNEL_FP64, sv[0]->reg_w4, sv[0]->reg_r,
+                               G, s));
+            HIP_TRY(hipEventRecord(e1, s));
+            std::vector<unsigned long long> w(4 * (size_t)G);
+            for (const RegArgs& r : ra) {
+                HIP_TRY(hipMemcpyAsync(w.data(), r.work, sizeof(unsigned long long) * w.size(), hipMemcpyDeviceToHost, s));
+                HIP_TRY(hipStreamSynchronize(s));
+                for (int b = 0; b < G; ++b) rows += w[4 * b];
+            }
+        } else {
+            SharedArgs a{};
+            a.n = n; a.d = d; a.dpad = dpad_of(d); a.lay = lay;
+            a.wpr = lay == LAY_BITS ? bits_wpr(d) : 0;
+            a.k = k;
+            a.live_mask = running;
+            a.seg_max = seg_max;
+            a.res = res ? 1 : 0;
+            a.x = sv[0]->xin;
+            a.bits = sv[0]->bits;
+            a.rec = rec;
+            a.spin_limit = 500ull * 1000 * 1000;   // 5 s of the 100 MHz wall clock per record wait
+            a.work = work;
+            for (int p = 0; p < k; ++p) {
+                SharedProb& b = a.prob[p];
+                b.y = y[p]; b.alpha = alpha[p]; b.f = sv[p]->f; b.status = sv[p]->status; b.ctl = sv[p]->ctl;
+                b.C = params[p].C; b.gamma = params[p].gamma; b.thr = 2.0 * params[p].eps; b.max_iter = params[p].max_iter;
+            }
+            HIP_TRY(hipMemsetAsync(rec, 0, sizeof(Rec) * 2 * SHARED_MAX * G, s));
+            HIP_TRY(hipEventRecord(e0, s));
+            HIP_TRY(launch_shared(a, G, kprec, s));
+            HIP_TRY(hipEventRecord(e1, s));
+            std::vector<unsigned long long> w(G);
+            HIP_TRY(hipMemcpyAsync(w.data(), work, sizeof(unsigned long long) * G, hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipStreamSynchronize(s));
+            for (int b = 0; b < G; ++b) rows += w[b];
         }
-        HIP_TRY(hipMemsetAsync(rec, 0, sizeof(Rec) * 2 * SHARED_MAX * G, s));
-        HIP_TRY(hipEventRecord(e0, s));
-        HIP_TRY(launch_shared(a, G, kprec, s));
-        HIP_TRY(hipEventRecord(e1, s));
-        HIP_TRY(hipEventSynchronize(e1));
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-        std::vector<unsigned long long> w(G);
-        HIP_TRY(hipMemcpy(w.data(), work, sizeof(unsigned long long) * G, hipMemcpyDeviceToHost));
-        unsigned long long rows = 0;
-        for (int b = 0; b < G; ++b) rows += w[b];
         const int launched = running;
         for (int p = 0; p < k; ++p) {
             if (!((launched >> p) & 1)) continue;

@@ -163,6 +163,11 @@ struct RegArgs {
     unsigned long long* work;
     const RegDebug* dbg;      // or NULL
 };
+// The problems of one launch, each on G workgroups of its own (blockIdx.y names the problem).
+constexpr int REG_PROBS = 8;
+struct RegLaunch {
+    RegArgs a[REG_PROBS];
+};
 // Rows a thread can hold (1, 2 or 4) of W4 * 16 bytes each: at most 160 of the 256 registers, the rest
 // being the f, status and distances of the rows and the working set; FP64 distances take twice theirs.
 constexpr int reg_rows_max(bool fp64, int W4) { return W4 * 4 <= 40 && !fp64 ? 4 : W4 * 2 <= 40 ? 2 : 1; }
@@ -174,7 +179,7 @@ int reg_rows(bool fp64, int W4, int nseg);
 const void* reg_fn_dense(bool fp64, int W4, int R);
 const void* reg_fn_bits(bool fp64, int W4, int R);
 int reg_max_blocks(int lay, bool fp64, int W4, int R);
-hipError_t launch_reg(const RegArgs& a, int lay, bool fp64, int W4, int R, int G, hipStream_t s);
+hipError_t launch_reg(const RegArgs* a, int k, int lay, bool fp64, int W4, int R, int G, hipStream_t s);
 
 // Kernel sums: out[a] = sum_b coef[b] * K(A_a, B_b) + bias_a, bias_a = -y_a or -beta.
 struct SumArgs {

@@ -17,6 +17,8 @@
 //    256 workgroups, against 3.2 / 4.0 / 4.8 with the 128-byte records of svm_step.hip on 1024
 //    threads (a record spread over word arrays, so that a lane reads a whole one, took 5.6 / 5.6 / 6.3);
 //  * up to 8 workgroups, wave 0 alone reads and merges the records.
+// A launch runs up to 8 problems of one sample set side by side (svm_train_shared), each on a row of
+// the grid (blockIdx.y) with its own records and state: their chains overlap, and nothing is shared.
 // Kernel values, the f update and the selection are those of svm_step.hip operation for operation,
 // so results are equal bit for bit.
 #pragma once
@@ -51,7 +53,8 @@ DEV void pin(T& v) { asm volatile("" : "+v"(v)); }
 
 // BITS: rows of 4 * W4 words; else rows of 4 * W4 floats (zeros beyond dpad).
 template <bool BITS, typename KT, int W4, int R>
-__global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegArgs A) {
+__global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
+    const RegArgs& A = L.a[blockIdx.y];
     constexpr int NT = REG_BLOCK, NW = REG_NW, W = 4 * W4;
     typedef typename std::conditional<BITS, uint4, float4>::type V4;
     __shared__ double s_al[R * NT];                               // alpha of the segment's rows

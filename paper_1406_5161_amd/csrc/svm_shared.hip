@@ -4,6 +4,9 @@
 // per pass for all of them.  Every problem's arithmetic is the single-problem loop's (the same
 // pair staging and K(up, low), the same distance, kernel value and eq:fup update, the exact
 // two-threshold selection of eq:bminmax), so each problem follows its own run's trajectory.
+// Problems that fit the chip side by side with their rows in registers do not come here: they run
+// in the loop of svm_regloop.h, each on workgroups of its own (the rule and both sides' times stand
+// at shared_own_grid in svm_host.cpp).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

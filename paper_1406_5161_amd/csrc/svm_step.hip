@@ -989,12 +989,13 @@ int reg_max_blocks(int lay, bool fp64, int W4, int R) {
     return nb * device_cu_count();
 }
 
-hipError_t launch_reg(const RegArgs& a, int lay, bool fp64, int W4, int R, int G, hipStream_t s) {
+hipError_t launch_reg(const RegArgs* a, int k, int lay, bool fp64, int W4, int R, int G, hipStream_t s) {
     const void* fn = reg_fn(lay, fp64, W4, R);
-    if (!fn || G < 1 || G > REG_GRID_MAX) return hipErrorInvalidValue;
-    RegArgs copy = a;
-    void* args[] = {&copy};
-    return hipLaunchCooperativeKernel(fn, dim3(G), dim3(REG_BLOCK), args, 0, s);
+    if (!fn || G < 1 || G > REG_GRID_MAX || k < 1 || k > REG_PROBS) return hipErrorInvalidValue;
+    RegLaunch l{};
+    for (int p = 0; p < k; ++p) l.a[p] = a[p];
+    void* args[] = {&l};
+    return hipLaunchCooperativeKernel(fn, dim3(G, k), dim3(REG_BLOCK), args, 0, s);
 }
 
 int step_max_blocks(int lay, int lpr, int kprec, int mode, size_t lds, bool cache) {
