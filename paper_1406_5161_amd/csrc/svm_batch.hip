@@ -42,6 +42,8 @@ struct BatchShared {
     int tseli[2];
     long long tcnt;
     int tok;
+    int tlate;                               // a wait for selection records has expired
+    unsigned long long rec8[TEAM_MAX * 9];   // the team's selection records (odd stride)
     double tsum[6];
     unsigned long long pt[9];   // per-phase timer of rank 0 (slots as in svm_debug_set_profile's batch use)
     int pr[5];                  // preparation job: err, n_pos, n_neg, max_row_nnz, not-pattern
@@ -319,7 +321,7 @@ DEV bool team_read(const unsigned long long* trec, int B, unsigned seq, unsigned
     const int lane = threadIdx.x & 63;
     bool ok = true;
     if (lane < B) {
-        const unsigned long long* w = trec + ((size_t)(seq & 1) * B + lane) * 16;
+        const unsigned long long* w = in_device(trec) + ((size_t)(seq & 1) * B + lane) * 16;
         const unsigned long long t0 = wall_clock64();
         while ((unsigned)(ld_agent(w + REC_WORDS - 1) >> 32) != seq) {
             if (wall_clock64() - t0 > spin_limit) { ok = false; break; }
@@ -349,7 +351,7 @@ DEV void team_write(unsigned long long* trec, int B, int rank, unsigned seq, con
     for (int k = 1; k < REC_WORDS; ++k)
         if (lane == k) x = v[k];
     if (lane < REC_WORDS) {
-        unsigned long long* w = trec + ((size_t)(seq & 1) * B + rank) * 16;
+        unsigned long long* w = in_device(trec) + ((size_t)(seq & 1) * B + rank) * 16;
         st_agent(w + lane, ((unsigned long long)seq << 32) | x);
     }
 }
@@ -375,48 +377,100 @@ DEV double unpack_d(const unsigned* v, int k) {
 }
 
 // Merge the members' candidates (called by every thread; every lane of wave 0 holds this
-// member's values).
+// member's values).  Records of one 64-byte line, eight words of 48 payload bits and a 16-bit tag,
+// read eight per load instruction, as in svm_regloop.h.  A tag cannot be an old one: a member
+// writes each of its two records again within a few exchanges.  The caller's next write to the
+// merged values is behind at least one barrier (the pair staging's, select_block's).
 DEV TeamSel team_select(const BatchDesc& P, int rank, unsigned seq, double bu, int iu, double au, double bl,
                         int il, double al, long long cnt, BatchShared& sh) {
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, B = P.team;
     TeamSel r;
-    if (P.team == 1) {
+    if (B == 1) {
         if (tid == 0) {
             sh.tsel[0] = bu; sh.tsel[1] = bl; sh.tsel[2] = au; sh.tsel[3] = al;
-            sh.tseli[0] = iu; sh.tseli[1] = il; sh.tcnt = cnt; sh.tok = 1;
+            sh.tseli[0] = iu; sh.tseli[1] = il; sh.tcnt = cnt;
         }
     } else {
-        if (tid < 64) {
-            unsigned v[REC_WORDS];
-            pack_d(v, 0, bu); pack_d(v, 2, bl); pack_d(v, 4, au); pack_d(v, 6, al);
-            v[8] = (unsigned)iu; v[9] = (unsigned)il;
-            v[10] = (unsigned)(cnt & 0xffffffffll); v[11] = (unsigned)((unsigned long long)cnt >> 32);
-            v[12] = v[13] = v[14] = 0;
-            team_write(P.trec, P.team, rank, seq, v);
-        }
-        if (tid < 64) {
-            unsigned v[REC_WORDS];
-            const bool ok = team_read(P.trec, P.team, seq, v, seq == 1 ? TEAM_GATHER_TICKS : TEAM_WAIT_TICKS);
-            const int lane = tid;
-            double xbu = INFINITY, xbl = -INFINITY, xau = 0.0, xal = 0.0;
-            int xiu = IDX_NONE, xil = IDX_NONE;
-            long long xc = 0;
-            if (lane < P.team && ok) {
-                xbu = unpack_d(v, 0); xbl = unpack_d(v, 2); xau = unpack_d(v, 4); xal = unpack_d(v, 6);
-                xiu = (int)v[8]; xil = (int)v[9];
-                xc = (long long)(((unsigned long long)v[11] << 32) | v[10]);
+        const int lane = tid & 63, wid = tid >> 6, sub = lane >> 3;
+        const unsigned tg = seq & 0xffffu;
+        unsigned long long* rec = in_device(P.trec) + (size_t)32 * B + (size_t)(seq & 1) * 8 * B;
+        if (tid < 8) {
+            const unsigned long long bub = (unsigned long long)__double_as_longlong(bu);
+            const unsigned long long blb = (unsigned long long)__double_as_longlong(bl);
+            const unsigned long long aub = (unsigned long long)__double_as_longlong(au);
+            const unsigned long long alb = (unsigned long long)__double_as_longlong(al);
+            unsigned long long x;
+            switch (lane) {
+                case 0: x = bub & REC8_MASK; break;
+                case 1: x = blb & REC8_MASK; break;
+                case 2: x = aub & REC8_MASK; break;
+                case 3: x = alb & REC8_MASK; break;
+                case 4: x = (bub >> 48) | ((unsigned long long)(unsigned)iu << 16); break;
+                case 5: x = (blb >> 48) | ((unsigned long long)(unsigned)il << 16); break;
+                case 6: x = (aub >> 48) | ((unsigned long long)(unsigned)cnt << 16); break;
+                default: x = alb >> 48; break;
             }
-            const int myiu = xiu, myil = xil;
+            st_agent(rec + 8 * rank + lane, ((unsigned long long)tg << 48) | x);
+        }
+        // up to 16 members wave 0 alone reads the records, beyond that every wave its share
+        const int readers = B <= 16 ? 1 : BNW;
+        if (wid < readers) {
+            constexpr int QW = 2;
+            unsigned long long x[QW];
+            bool ok[QW], ab = false;
+#pragma unroll
+            for (int j = 0; j < QW; ++j) {
+                ok[j] = 8 * (wid + readers * j) + sub >= B;
+                x[j] = 0;
+            }
+            const unsigned long long t0 = wall_clock64(), limit = seq == 1 ? TEAM_GATHER_TICKS : TEAM_WAIT_TICKS;
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int j = 0; j < QW; ++j) {
+                    if (!ok[j]) {
+                        x[j] = ld_agent(rec + 64 * (wid + readers * j) + lane);
+                        ok[j] = (unsigned)(x[j] >> 48) == tg;
+                    }
+                    all = all && ok[j];
+                }
+                if (__all(all)) break;
+                if (wall_clock64() - t0 > limit) { ab = true; break; }
+            }
+#pragma unroll
+            for (int j = 0; j < QW; ++j) {
+                const int m = 8 * (wid + readers * j) + sub;
+                if (m < B) sh.rec8[m * 9 + (lane & 7)] = x[j] & REC8_MASK;
+            }
+            if (ab) sh.tlate = 1;
+        }
+        if (readers > 1) __syncthreads();
+        else wave_lds_fence();
+        if (tid < 64) {
+            double xbu = INFINITY, xbl = -INFINITY, xau = 0.0, xal = 0.0;
+            int xiu = IDX_NONE, xil = IDX_NONE, xc = 0;
+            if (lane < B) {
+                const unsigned long long* w = sh.rec8 + lane * 9;
+                const unsigned long long w4 = w[4], w5 = w[5], w6 = w[6], w7 = w[7];
+                xbu = rec8_double(w[0], w4);
+                xbl = rec8_double(w[1], w5);
+                xau = rec8_double(w[2], w6);
+                xal = rec8_double(w[3], w7);
+                xiu = (int)(unsigned)(w4 >> 16);
+                xil = (int)(unsigned)(w5 >> 16);
+                xc = (int)(unsigned)(w6 >> 16);
+            }
             // active-row counts: the team's total is at most n < 2^31
-            const long long tot = wave_sum_i32_dpp((int)xc);
-            wave_reduce_sel(xbu, xiu, xbl, xil);
-            if (lane < P.team && myiu == xiu && xiu != IDX_NONE) sh.tsel[2] = xau;
-            if (lane < P.team && myil == xil && xil != IDX_NONE) sh.tsel[3] = xal;
+            const long long tot = wave_sum_i32_dpp(xc);
+            int wu, wl;
+            wave_reduce_sel(xbu, xiu, xbl, xil, wu, wl);
+            xau = readlane_d(xau, wu);
+            xal = readlane_d(xal, wl);
             if (lane == 0) {
-                sh.tsel[0] = xbu; sh.tsel[1] = xbl; sh.tseli[0] = xiu; sh.tseli[1] = xil; sh.tcnt = tot;
-                sh.tok = ok ? 1 : 0;
-                if (xiu == IDX_NONE) sh.tsel[2] = 0.0;
-                if (xil == IDX_NONE) sh.tsel[3] = 0.0;
+                sh.tsel[0] = xbu; sh.tsel[1] = xbl;
+                sh.tsel[2] = xiu == IDX_NONE ? 0.0 : xau;
+                sh.tsel[3] = xil == IDX_NONE ? 0.0 : xal;
+                sh.tseli[0] = xiu; sh.tseli[1] = xil; sh.tcnt = tot;
             }
         }
     }
@@ -425,8 +479,7 @@ DEV TeamSel team_select(const BatchDesc& P, int rank, unsigned seq, double bu, i
     r.iu = sh.tseli[0] == IDX_NONE ? -1 : sh.tseli[0];
     r.il = sh.tseli[1] == IDX_NONE ? -1 : sh.tseli[1];
     r.cnt = sh.tcnt;
-    r.ok = sh.tok;
-    __syncthreads();
+    r.ok = sh.tlate == 0;
     return r;
 }
 
@@ -671,12 +724,21 @@ __device__ __attribute__((noinline)) void kernel_sum_block(const BatchDesc& P, c
     }
 }
 
+// What bounds an iteration with the rows in LDS is the chain pair rows -> row pass -> block reduction ->
+// exchange, not the rows: the row pass takes as few rows at a time as a lane group has (four rows a
+// group where one is there cost 2.1 us against 1.2 with 300 bits, 3.2 against 1.8 with 20 columns),
+// LDS and device memory are accessed as such (through pointers of unknown memory the same pass waits
+// for both), the candidates' alpha comes from LDS, and a record is one 64-byte line (exchange of 32
+// members 2.1 us against 2.6 with 128-byte records read word by word).  300-bit rows, n = 8000, 32
+// members: 5.98 -> 4.30 us an iteration; 128 dense columns, n = 7308, 64 members: 10.5 -> 7.7.
 // One member (rank) of the team of P.team workgroups solving problem P.  Member b owns rows
 // [n b / B, n (b+1) / B); the members run the same driver, take the same decisions from the
 // merged selections, and meet only in team exchanges.
 // (one instance per kernel precision and row layout, each with its own register allocation)
 template <typename KT, int LAYK>
-__device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned char* dyn) {
+__device__ __attribute__((noinline)) void solve_team(BatchShared& shm, unsigned char* dynm) {
+    BatchShared& sh = *in_lds(&shm);
+    unsigned char* const dyn = in_lds(dynm);
     const BatchDesc& P = sh.P;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int n = P.n, B = P.team, rank = sh.rank;
@@ -730,6 +792,17 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
     uint16_t* cols_l = reinterpret_cast<uint16_t*>(segmem + so);
     if (!dense && !bits) so += al16(sizeof(uint16_t) * (size_t)nnz_seg);
     float* vals_l = reinterpret_cast<float*>(segmem + so);
+    // the rows' alpha beside them, if that fits too (the candidates' values are on the exchange's way)
+    const size_t al_off = state_bytes + rows_bytes;
+    const bool ares = rres && al_off + sizeof(double) * (size_t)m <= seg_room;
+    double* al_l = reinterpret_cast<double*>(segmem + al_off);
+    const int8_t* gy = in_device(P.y);
+    const float* gx = in_device(P.x);
+    const uint32_t* gbits = in_device(P.bits);
+    const int32_t* grp = in_device(P.row_ptr);
+    const int32_t* gcol = in_device(P.col);
+    const float* gval = in_device(P.val);
+    double* galpha = in_device(P.alpha);
     const unsigned long long t_start = wall_clock64();
     unsigned seq = 1;
     bool alive = true;
@@ -756,7 +829,9 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
         P.f[i] = yp ? -1.0 : 1.0;
         P.status[i] = st_make(yp, 0.0, C);
         act[i - seg0] = i;
+        if (ares) al_l[i - seg0] = 0.0;
     }
+    if (tid == 0) sh.tlate = 0;
     __syncthreads();
 
     int nact = seg1 - seg0;
@@ -769,8 +844,13 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
                      double ajl) {
         double cau = 0.0, cal = 0.0;
         if (tid < 64) {
-            if (ciu != IDX_NONE) cau = ciu == ju ? aju : ciu == jl ? ajl : ld_agent(P.alpha + ciu);
-            if (cil != IDX_NONE) cal = cil == ju ? aju : cil == jl ? ajl : ld_agent(P.alpha + cil);
+            if (ares) {
+                if (ciu != IDX_NONE) cau = al_l[ciu - seg0];
+                if (cil != IDX_NONE) cal = al_l[cil - seg0];
+            } else {
+                if (ciu != IDX_NONE) cau = ciu == ju ? aju : ciu == jl ? ajl : ld_agent(galpha + ciu);
+                if (cil != IDX_NONE) cal = cil == ju ? aju : cil == jl ? ajl : ld_agent(galpha + cil);
+            }
         }
         const TeamSel t = team_select(P, rank, seq++, cbu, ciu, cau, cbl, cil, cal, cnt, sh);
         bu = t.bu; bl = t.bl; au = t.au; al = t.al; iu = t.iu; il = t.il;
@@ -858,10 +938,10 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
         // ---- SMO iterations of this phase
         while (alive && bl - bu > thr) {
             if (iter >= P.max_iter) { status = SVM_NOT_CONVERGED; break; }
-            const int yu = P.y[iu] > 0 ? 1 : -1, yl = P.y[il] > 0 ? 1 : -1;
+            const int yu = gy[iu] > 0 ? 1 : -1, yl = gy[il] > 0 ? 1 : -1;
             if (dense) {
-                const float* xu = P.x + (size_t)iu * P.dpad;
-                const float* xl = P.x + (size_t)il * P.dpad;
+                const float* xu = gx + (size_t)iu * P.dpad;
+                const float* xl = gx + (size_t)il * P.dpad;
                 if constexpr (std::is_same<KT, double>::value) {
                     for (int k = tid; k < P.dpad; k += BB) pairv[k] = make_float2(xu[k], xl[k]);
                     __syncthreads();
@@ -894,8 +974,8 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
                     const int wpr = P.wpr;
                     uint32_t wu = 0, wl = 0;
                     if (lane < wpr) {
-                        wu = P.bits[(size_t)iu * wpr + lane];
-                        wl = P.bits[(size_t)il * wpr + lane];
+                        wu = gbits[(size_t)iu * wpr + lane];
+                        wl = gbits[(size_t)il * wpr + lane];
                         pairb[lane] = wu;
                         pairb[wpr + lane] = wl;
                     }
@@ -911,25 +991,25 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
                     }
                 }
             } else {
-                const int pu0 = P.row_ptr[iu], pu1 = P.row_ptr[iu + 1];
-                const int pl0 = P.row_ptr[il], pl1 = P.row_ptr[il + 1];
+                const int pu0 = grp[iu], pu1 = grp[iu + 1];
+                const int pl0 = grp[il], pl1 = grp[il + 1];
                 const int nu = pu1 - pu0, nl = pl1 - pl0;
                 for (int k = tid; k < P.d; k += BB) pairv[k] = make_float2(0.f, 0.f);
                 __syncthreads();
                 float* pf = reinterpret_cast<float*>(pairv);
-                for (int p = tid; p < nu; p += BB) pf[2 * P.col[pu0 + p]] = pat ? 1.f : P.val[pu0 + p];
-                for (int p = tid; p < nl; p += BB) pf[2 * P.col[pl0 + p] + 1] = pat ? 1.f : P.val[pl0 + p];
+                for (int p = tid; p < nu; p += BB) pf[2 * gcol[pu0 + p]] = pat ? 1.f : gval[pu0 + p];
+                for (int p = tid; p < nl; p += BB) pf[2 * gcol[pl0 + p] + 1] = pat ? 1.f : gval[pl0 + p];
                 __syncthreads();
                 if (wid == 0) {
                     KT su = 0, sl = 0, dot = 0;
                     for (int p = lane; p < nu; p += 64) {
-                        const KT v = P.pattern_only ? (KT)1 : (KT)P.val[pu0 + p];
+                        const KT v = P.pattern_only ? (KT)1 : (KT)gval[pu0 + p];
                         su += v * v;
                     }
                     for (int p = lane; p < nl; p += 64) {
-                        const KT v = P.pattern_only ? (KT)1 : (KT)P.val[pl0 + p];
+                        const KT v = P.pattern_only ? (KT)1 : (KT)gval[pl0 + p];
                         sl += v * v;
-                        dot += v * (KT)pairv[P.col[pl0 + p]].x;
+                        dot += v * (KT)pairv[gcol[pl0 + p]].x;
                     }
                     su = wave_sum(su);
                     sl = wave_sum(sl);
@@ -956,62 +1036,77 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
             double cbu = INFINITY, cbl = -INFINITY;
             int ciu = IDX_NONE, cil = IDX_NONE;
             int newcount = 0;
-            constexpr int RPT = 4;
-            for (int base = 0; base < nact; base += NG * RPT) {
-                int ii[RPT], rr[RPT];
-                bool vv[RPT];
+            // (RP rows of a lane group at a time; RR: rows and state in LDS)
+            auto stream = [&](auto rp, auto rr_) __attribute__((always_inline)) {
+                constexpr int RPT = decltype(rp)::value;
+                constexpr bool RR = decltype(rr_)::value;
+                for (int base = 0; base < nact; base += NG * RPT) {
+                    int ii[RPT], rr[RPT];
+                    bool vv[RPT];
 #pragma unroll
-                for (int r = 0; r < RPT; ++r) {
-                    const int t = base + r * NG + g;
-                    vv[r] = t < nact;
-                    rr[r] = vv[r] ? (res ? (int)act_l[t] : act[t] - seg0) : 0;
-                    ii[r] = seg0 + rr[r];
-                }
-                KT du2[RPT], dl2[RPT];
-                if (bits)
-                    rows_dist_bits<KT, RPT>(P.wpr, rres ? bits_l : P.bits, pairb, rres ? rr : ii, vv, nuu, nll, du2,
-                                            dl2);
-                else if (rres)
-                    rows_dist<KT, RPT>(dense, P.dpad, x_l, off_l, cols_l, vals_l, pat, pairv, rr, vv, gl, lpr, nuu,
-                                       nll, du2, dl2);
-                else
-                    rows_dist<KT, RPT>(dense, P.dpad, P.x, P.row_ptr, P.col, P.val, pat, pairv, ii, vv, gl, lpr,
-                                       nuu, nll, du2, dl2);
-                bool keep[RPT];
+                    for (int r = 0; r < RPT; ++r) {
+                        const int t = base + r * NG + g;
+                        vv[r] = t < nact;
+                        rr[r] = vv[r] ? (RR || res ? (int)act_l[t] : act[t] - seg0) : 0;
+                        ii[r] = seg0 + rr[r];
+                    }
+                    KT du2[RPT], dl2[RPT];
+                    if constexpr (bits) {
+                        if constexpr (RR)
+                            rows_dist_bits<KT, RPT>(P.wpr, bits_l, pairb, rr, vv, nuu, nll, du2, dl2);
+                        else
+                            rows_dist_bits<KT, RPT>(P.wpr, gbits, pairb, ii, vv, nuu, nll, du2, dl2);
+                    } else if constexpr (RR) {
+                        rows_dist<KT, RPT>(dense, P.dpad, x_l, off_l, cols_l, vals_l, pat, pairv, rr, vv, gl, lpr, nuu,
+                                           nll, du2, dl2);
+                    } else {
+                        rows_dist<KT, RPT>(dense, P.dpad, gx, grp, gcol, gval, pat, pairv, ii, vv, gl, lpr, nuu, nll,
+                                           du2, dl2);
+                    }
+                    bool keep[RPT];
 #pragma unroll
-                for (int r = 0; r < RPT; ++r) {
-                    keep[r] = false;
-                    const int i = ii[r];
-                    if (vv[r] && gl == 0) {
-                        const double ku = (i == iu) ? 1.0 : (double)kexp(-gam * du2[r]);
-                        const double kl = (i == il) ? 1.0 : (double)kexp(-gam * dl2[r]);
-                        double* fp = res ? f_l + rr[r] : P.f + i;
-                        uint8_t* sp = res ? st_l + rr[r] : P.status + i;
-                        double fi;
-                        {
+                    for (int r = 0; r < RPT; ++r) {
+                        keep[r] = false;
+                        const int i = ii[r];
+                        if (vv[r] && gl == 0) {
+                            const double ku = (i == iu) ? 1.0 : (double)kexp(-gam * du2[r]);
+                            const double kl = (i == il) ? 1.0 : (double)kexp(-gam * dl2[r]);
+                            double* fp = RR || res ? f_l + rr[r] : P.f + i;
+                            uint8_t* sp = RR || res ? st_l + rr[r] : P.status + i;
+                            double fi;
+                            {
 #pragma clang fp contract(off)
-                            fi = *fp + (pn.cu * ku + pn.cl * kl);
-                        }
-                        *fp = fi;
-                        uint8_t st = *sp;
-                        if (i == iu) {
-                            st = st_make(yu > 0, pn.au, C);
-                            *sp = st;
-                            st_agent(P.alpha + i, pn.au);
-                        } else if (i == il) {
-                            st = st_make(yl > 0, pn.al, C);
-                            *sp = st;
-                            st_agent(P.alpha + i, pn.al);
-                        }
-                        keep[r] = !(do_shrink && shrink_rule(st, fi, bu, bl));
-                        if (!keep[r]) *sp = st | 8;
-                        if (keep[r]) {
-                            if (st_in_up(st) && better_up(fi, i, cbu, ciu)) { cbu = fi; ciu = i; }
-                            if (st_in_low(st) && better_low(fi, i, cbl, cil)) { cbl = fi; cil = i; }
+                                fi = *fp + (pn.cu * ku + pn.cl * kl);
+                            }
+                            *fp = fi;
+                            uint8_t st = *sp;
+                            if (i == iu) {
+                                st = st_make(yu > 0, pn.au, C);
+                                *sp = st;
+                                st_agent(galpha + i, pn.au);
+                                if (ares) al_l[rr[r]] = pn.au;
+                            } else if (i == il) {
+                                st = st_make(yl > 0, pn.al, C);
+                                *sp = st;
+                                st_agent(galpha + i, pn.al);
+                                if (ares) al_l[rr[r]] = pn.al;
+                            }
+                            keep[r] = !(do_shrink && shrink_rule(st, fi, bu, bl));
+                            if (!keep[r]) *sp = st | 8;
+                            if (keep[r]) {
+                                if (st_in_up(st) && better_up(fi, i, cbu, ciu)) { cbu = fi; ciu = i; }
+                                if (st_in_low(st) && better_low(fi, i, cbl, cil)) { cbl = fi; cil = i; }
+                            }
                         }
                     }
                 }
-            }
+            };
+            using std::integral_constant;
+            // as many rows at a time as the list has for a lane group: rows beyond its end cost what rows do
+            if (!rres) stream(integral_constant<int, 4>{}, integral_constant<bool, false>{});
+            else if (nact <= NG) stream(integral_constant<int, 1>{}, integral_constant<bool, true>{});
+            else if (nact <= 2 * NG) stream(integral_constant<int, 2>{}, integral_constant<bool, true>{});
+            else stream(integral_constant<int, 4>{}, integral_constant<bool, true>{});
             if (do_shrink) {
                 // rows the rule removed carry the shrunk bit: one stable in-place compaction of
                 // the list after the pass (each chunk is read before its first barrier and
@@ -1035,8 +1130,9 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& sh, unsigned c
                 }
             }
             lap(1);
-            block_reduce_sel_all<BB>(cbu, ciu, cbl, cil, sh.v, sh.i);
+            waves_to_lds<BB>(cbu, ciu, cbl, cil, sh.v, sh.i);
             __syncthreads();
+            if (wid == 0) wave_reduce_waves<BB>(cbu, ciu, cbl, cil, sh.v, sh.i);   // (merge has a barrier after)
             lap(2);
             if (do_shrink) nact = newcount;
             const long long tot = merge(cbu, ciu, cbl, cil, nact, iu, pn.au, il, pn.al);
@@ -1230,7 +1326,7 @@ DEV void prep_job(BatchShared& sh) {
             if (cw >= 0) out[(size_t)i * wpr + cw] |= acc;
         }
     }
-    for (int k = tid; k < 2 * 16 * TEAM_MAX; k += BB) P.trec[k] = 0ull;
+    for (int k = tid; k < TEAM_REC * TEAM_MAX; k += BB) P.trec[k] = 0ull;
     if (err) atomicOr(&sh.pr[0], err);
     if (npos) atomicAdd(&sh.pr[1], npos);
     if (nneg) atomicAdd(&sh.pr[2], nneg);

@@ -340,6 +340,19 @@ DEV void block_reduce_sel(double& bu, int& iu, double& bl, int& il, double* s_v,
     __syncthreads();
 }
 
+// Words of a 64-byte selection record: 48 payload bits and, above, a 16-bit tag.
+constexpr unsigned long long REC8_MASK = 0xffffffffffffull;   // payload bits of a record word
+DEV double rec8_double(unsigned long long lo48, unsigned long long hi) {
+    return __longlong_as_double((long long)((lo48 & REC8_MASK) | (hi << 48)));
+}
+
+// Pointers known to point into LDS or device memory: accesses through them take the instructions of
+// that memory where the compiler cannot tell (pointers handed on through memory or calls).
+template <typename T>
+DEV T* in_lds(T* p) { return (T*)(__attribute__((address_space(3))) T*)p; }
+template <typename T>
+DEV T* in_device(T* p) { return (T*)(__attribute__((address_space(1))) T*)p; }
+
 // ------------------------------------------------------------------ pair update (eq:alphaup, eq:rho)
 
 struct PairNew {

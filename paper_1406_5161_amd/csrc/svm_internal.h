@@ -398,6 +398,7 @@ constexpr int BATCH_BLOCK = 512;
 constexpr size_t BATCH_LDS_BYTES = 120 * 1024;   // dynamic LDS of a batched workgroup
 constexpr int BATCH_SUMR = 8;                     // rows per reconstruction tile
 constexpr int TEAM_MAX = 64;                      // workgroups per problem (one wave merges them)
+constexpr int TEAM_REC = 2 * (16 + 8);            // 8-byte words of a member's exchange records: sums, selections
 
 struct BatchResult {
     double beta, b_up, b_low, dual_obj;
@@ -436,7 +437,7 @@ struct BatchDesc {
     int32_t pad;
     int32_t team;                        // workgroups solving this problem together
     int32_t team_min;                    // BatchArgs::join: the team starts with this many if no more are free
-    unsigned long long* trec;            // team exchange records [2][team][16], zeroed before the start
+    unsigned long long* trec;            // team exchange records [2][team][16] and [2][team][8], zeroed before the start
     unsigned long long* prof;            // NULL, or 8 device counters rank 0 adds its phase ticks to
     // preparation jobs only (ticket rank -1): the caller's samples, validated and, for dense
     // layouts, packed into x; the team records (TEAM_MAX members) are zeroed

@@ -42,11 +42,6 @@ DEV int rst_make(int st, bool active) {
     return st | (active ? RST_ACTIVE : 0) | (st_in_up(s) ? RST_UP : 0) | (st_in_low(s) ? RST_LOW : 0);
 }
 
-constexpr unsigned long long REC8_MASK = 0xffffffffffffull;   // payload bits of a record word
-DEV double rec8_double(unsigned long long lo48, unsigned long long hi) {
-    return __longlong_as_double((long long)((lo48 & REC8_MASK) | (hi << 48)));
-}
-
 // A value that the compiler takes as formed at this place and unknown from here on.
 template <typename T>
 DEV void pin(T& v) { asm volatile("" : "+v"(v)); }

@@ -85,7 +85,7 @@ ProbBytes prob_bytes(const svm_problem_t* p, bool need_f, int team, int rec_memb
     b.status = take(n);
     b.act = take(sizeof(int32_t) * n);
     b.lw = take(sizeof(int32_t) * n);
-    b.trec = take(sizeof(unsigned long long) * 2 * 16 * rec_members);
+    b.trec = take(sizeof(unsigned long long) * TEAM_REC * rec_members);
     b.base = o;
     o = 0;
     b.lz = take(sizeof(int32_t) * n * team);
@@ -154,14 +154,15 @@ int team_size(const svm_problem_t* p, const Inspect& in, int workers, int reques
 }
 
 // Give the workgroups that the teams of a batch leave idle to the problems with the most to gain.  An
-// iteration costs about 6 us whatever the team (pair staging, reductions, the exchange: 2.4 us from two
-// members up, 3.1 with 64) and `row` us per row a member holds; a solve takes of the order of n
+// iteration costs about 3.5 us whatever the team (pair staging, reductions, the exchange: 1.5 us with two
+// members, 2.3 with 64) and `row` us per row a member holds; a solve takes of the order of n
 // iterations, but from a tenth of that to twice it, so each next member goes where n times the rows'
-// part is largest (24 problems of 1000 to 8000 samples: 59.7 ms; by the whole expected time, 63.9; without this rule, 147.1).  Measured for one problem alone, least team -> 32 members: 128 dense columns, n = 7308,
-// 136.8 -> 43.9 ms; 300-bit rows, n = 8000, 79.7 -> 54.1 ms; 20 columns, n = 6677, 5.5 -> 4.7 ms.
-// Below 0.5 us of rows a member a larger team gains nothing (the same three at 64: 38.6, 55.9, 4.7),
-// and a second member pays for its exchange from 4 us of rows on (20 columns, n = 1312, 3.5 us:
-// 5.3 ms alone, 5.6 with two).  The first sizes stay the least that a team may start with.
+// part is largest (24 problems of 1000 to 8000 samples, with the loop as it was then: 59.7 ms; by the
+// whole expected time, 63.9; without this rule, 147.1).  Measured for one problem alone, least team ->
+// 32 -> 64 members: 128 dense columns, n = 7308, 124 -> 42.2 -> 28.4 ms; 300-bit rows, n = 8000,
+// 71.8 -> 39.0 -> 41.6 ms.  Below 0.5 us of rows a member a larger team gains nothing, and a second
+// member pays for its exchange from 2 us of rows on (20 columns, n = 1000, 2.7 us: 2.77 ms alone, 2.48
+// with two).  The first sizes stay the least that a team may start with.
 void spread_teams(int k, const svm_problem_t* probs, const svm_params_t* params, const Inspect* ins, int workers,
                   std::vector<int>& team) {
     int64_t spare = workers;
@@ -176,7 +177,7 @@ void spread_teams(int k, const svm_problem_t* probs, const svm_params_t* params,
     std::priority_queue<Cand> q;
     auto push = [&](int p) {
         const double n = probs[p].n, t = rows[p] / team[p];
-        if (team[p] < TEAM_MAX && t >= 0.5 && (team[p] > 1 || t >= 4.0)) q.push(Cand{n * t, p});
+        if (team[p] < TEAM_MAX && t >= 0.5 && (team[p] > 1 || t >= 2.0)) q.push(Cand{n * t, p});
     };
     for (int p = 0; p < k; ++p) {
         if (params[p].grid_blocks > 0) continue;
@@ -298,7 +299,7 @@ int prepare(const svm_problem_t* p, const svm_params_t* q, const Inspect& in, in
     if (e == hipSuccess && bits_capable(p) && in.pattern)
         e = launch_pack_bits(p->n, p->d, bits_wpr(p->d), p->row_ptr, p->col, reinterpret_cast<uint32_t*>(ws + b.bits),
                              s);
-    if (e == hipSuccess) e = hipMemsetAsync(ws + b.trec, 0, sizeof(unsigned long long) * 2 * 16 * team, s);
+    if (e == hipSuccess) e = hipMemsetAsync(ws + b.trec, 0, sizeof(unsigned long long) * TEAM_REC * team, s);
     if (e != hipSuccess) return SVM_EHIP;
     fill_desc(p, q, in, team, team, alpha, f_user, ws, ws + b.base, res, D);
     return SVM_OK;

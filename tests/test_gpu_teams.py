@@ -72,3 +72,30 @@ def test_launches_that_overlap():
     assert not err
     for a, b in zip(ref, got):
         same(a, b)
+
+
+@pytest.mark.parametrize("kind", ["dense", "wide", "bits", "values"])
+def test_rows_per_member(kind):
+    """Members with rows for one, two and four rows a lane group, in LDS or streamed, with room for alpha
+    in LDS or not; 17 members and up read the records with every wave."""
+    import torch
+    from paper_1406_5161_amd import svmhip as S
+    r = np.random.default_rng([7, len(kind)])
+    n = 4200
+    data = (g.gen_blobs(n, 20, r) if kind == "dense" else g.gen_blobs(n, 160, r) if kind == "wide"
+            else g.gen_sparse_binary(n, 300, 0.12, r))
+    if kind == "values":
+        data.val = (data.val * r.uniform(0.5, 1.5, len(data.val))).astype(np.float32)
+    dp = S.to_device(data)
+    a0, f0 = (torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(2))
+    base = None
+    for team in (1, 2, 3, 4, 5, 8, 9, 16, 17, 33, 63, 64):
+        p = S.make_params(3.0, 0.01, 1e-3, 2, 1, 0.05, 1200, S.SVM_KERNEL_FP32)
+        p.grid_blocks = team
+        rc, res = S.svm_train_batch([dp], [p], [a0], [f0])
+        assert rc >= 0 and res[0].grid_blocks == team
+        got = (res[0].iterations, res[0].shrink_passes, res[0].shrunk_total, res[0].n_sv, res[0].beta)
+        if base is None:
+            base = (got, a0.clone(), f0.clone())
+        assert got == base[0]
+        assert torch.equal(a0, base[1]) and torch.equal(f0, base[2])
