@@ -340,6 +340,16 @@ DEV void block_reduce_sel(double& bu, int& iu, double& bl, int& il, double* s_v,
     __syncthreads();
 }
 
+// Whether a wait for records since t0 is over its limit.  The first exchange of a launch (whose start
+// state ctl still holds) waits 32 times as long (5 s -> 160 s): until all workgroups run, which other
+// work may hold up (a serving loop keeps all but eight compute units).
+DEV bool wait_expired(unsigned long long t0, unsigned long long limit, const Ctl* ctl, long long iter) {
+    const unsigned long long t = wall_clock64() - t0;
+    if (t <= limit) return false;
+    const long long at = (long long)ld_agent(reinterpret_cast<const unsigned long long*>(&ctl->iter));
+    return iter != at || t > 32 * limit;
+}
+
 // Words of a 64-byte selection record: 48 payload bits and, above, a 16-bit tag.
 constexpr unsigned long long REC8_MASK = 0xffffffffffffull;   // payload bits of a record word
 DEV double rec8_double(unsigned long long lo48, unsigned long long hi) {

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
                             all = all && ok[j];
                         }
                         if (__all(all)) break;
-                        if (wall_clock64() - t0 > A.spin_limit) { ab = true; break; }
+                        if (wait_expired(t0, A.spin_limit, ctl, iter)) { ab = true; break; }
                     }
 #pragma unroll
                     for (int j = 0; j < QW; ++j) {

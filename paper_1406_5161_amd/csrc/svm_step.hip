@@ -760,7 +760,7 @@ __global__ __launch_bounds__(STEP_BLOCK) void smo_loop_kernel(StepArgs A) {
                             all = all && ok[j];
                         }
                         if (__all(all)) break;
-                        if (wall_clock64() - t0 > A.spin_limit) { ab = 1; break; }
+                        if (wait_expired(t0, A.spin_limit, ctl, iter)) { ab = 1; break; }
                         __builtin_amdgcn_s_sleep(1);
                     }
 #pragma unroll
