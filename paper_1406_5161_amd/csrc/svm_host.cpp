@@ -1062,8 +1062,8 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
     bool each = own > 0;              // every problem on workgroups of its own
     for (int p = 0; p < k; ++p) each = each && sv[p]->reg_r && sv[p]->G == own;
     each = each && reg_max_blocks(lay, kprec == SVM_KERNEL_FP64, sv[0]->reg_w4, sv[0]->reg_r) >= k * own;
-    // else one pass over the rows serves every problem: about 700 rows per workgroup (at most SHARED_GRID_MAX); each workgroup keeps its segment's
-    // rows, f and status in LDS when they fit
+    // else one pass over the rows serves every problem: about 700 rows per workgroup (at most
+    // SHARED_GRID_MAX); each workgroup keeps its segment's rows, f and status in LDS when they fit
     int G = std::max(1, std::min(SHARED_GRID_MAX, n <= 4096 ? 1 : (n + 350) / 700));
     int seg_max = (n + G - 1) / G;
     bool res = false;
@@ -1348,7 +1348,7 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     a.part = pt;
     int blocks = 0;
     if (!dense && d <= BITS_MAX_D) {
-        // binary rows on both sides: bitsets and popcounts (exact squared distances)
+        // binary rows on both sides: bitsets (exact squared distances)
         if (!((valt.flags | valq.flags) & VAL_NOT_ONES)) {
             a.lay = LAY_BITS;
             a.wpr = bits_wpr(d);

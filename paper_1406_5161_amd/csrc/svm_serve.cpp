@@ -19,7 +19,9 @@
 // Progress of teams: tickets are taken in order and a problem's tickets are
 // consecutive, so the oldest partly taken problem always has its missing
 // members among the workgroups that finish the problems before it; with at
-// least as many workgroups as the largest team, every team fills.
+// least as many workgroups as the largest team, every team fills.  A batch may
+// ask for larger teams than that (spread_teams): those start without the
+// members that do not come, so what has to fill is the same.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

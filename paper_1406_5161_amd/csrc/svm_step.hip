@@ -16,7 +16,9 @@
 // A workgroup owns a fixed segment of the samples for the whole launch and,
 // when it fits, keeps the segment's per-row state (f, status, active list,
 // CSR offsets) and even its row payload in LDS, so an iteration reads HBM
-// only for the working pair and the records.
+// only for the working pair and the records.  Dense and bitset rows that fit
+// the register file run in svm_regloop.h instead (unless a kernel-row cache or
+// a form of this loop is asked for).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
