@@ -359,10 +359,52 @@ __global__ __launch_bounds__(CMP_BLOCK) void compact_write_kernel(int n, const u
     }
 }
 
+// Up to CMP_SMALL rows a thread in one workgroup: count, offsets and list in one launch instead of three,
+// which for so few rows is all that their time is; with more, the three use more than one CU's loads.
+constexpr int CMP_SMALL = 4;
+template <int PRED>
+__global__ __launch_bounds__(CMP_BLOCK) void compact_small_kernel(int n, const uint8_t* mask, const double* alpha,
+                                                                  const int8_t* y, int32_t* list, double* coef,
+                                                                  int32_t* count_out) {
+    constexpr int NW = CMP_BLOCK / 64;
+    __shared__ int s_c[CMP_SMALL][NW];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    unsigned long long m[CMP_SMALL];
+#pragma unroll
+    for (int k = 0; k < CMP_SMALL; ++k) {
+        const int i = k * CMP_BLOCK + threadIdx.x;
+        m[k] = __ballot(i < n && pred_at<PRED>(i, mask, alpha));
+        if (lane == 0) s_c[k][wid] = __popcll(m[k]);
+    }
+    __syncthreads();
+    int base = 0;
+#pragma unroll
+    for (int k = 0; k < CMP_SMALL; ++k) {
+        const int i = k * CMP_BLOCK + threadIdx.x;
+        int off = base;
+        for (int w = 0; w < NW; ++w) {
+            off += w < wid ? s_c[k][w] : 0;
+            base += s_c[k][w];
+        }
+        if ((m[k] >> lane) & 1) {
+            off += __popcll(m[k] & ((1ull << lane) - 1ull));
+            list[off] = i;
+            if (coef) coef[off] = alpha[i] * (y[i] > 0 ? 1.0 : -1.0);
+        }
+    }
+    if (threadIdx.x == 0) *count_out = base;
+}
+
 hipError_t launch_compact(int n, int pred, const uint8_t* mask, const double* alpha, const int8_t* y,
                           int32_t* blk_cnt, int32_t* list, double* coef, int32_t* count_out, hipStream_t s) {
     const int nb = (n + CMP_BLOCK - 1) / CMP_BLOCK;
     if (nb == 0) return hipMemsetAsync(count_out, 0, sizeof(int32_t), s);
+    if (nb <= CMP_SMALL) {
+        if (pred == 0) compact_small_kernel<0><<<1, CMP_BLOCK, 0, s>>>(n, mask, alpha, y, list, coef, count_out);
+        else if (pred == 1) compact_small_kernel<1><<<1, CMP_BLOCK, 0, s>>>(n, mask, alpha, y, list, coef, count_out);
+        else compact_small_kernel<2><<<1, CMP_BLOCK, 0, s>>>(n, mask, alpha, y, list, coef, count_out);
+        return hipGetLastError();
+    }
     if (pred == 0) compact_count_kernel<0><<<nb, CMP_BLOCK, 0, s>>>(n, mask, alpha, blk_cnt);
     else if (pred == 1) compact_count_kernel<1><<<nb, CMP_BLOCK, 0, s>>>(n, mask, alpha, blk_cnt);
     else compact_count_kernel<2><<<nb, CMP_BLOCK, 0, s>>>(n, mask, alpha, blk_cnt);

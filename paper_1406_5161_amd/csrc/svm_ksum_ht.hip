@@ -2,7 +2,7 @@
 // closing recompute and the classifier of eq:classi) with the dot products split by column
 // frequency: the H most frequent columns of the training set form a dense "head" row per
 // sample, multiplied on the matrix cores; the remaining "tail" nonzeros are matched through a
-// hash table of the target rows' tail columns in LDS.  Both parts are sums of FP32 products:
+// bitmap of the target rows' tail columns in LDS.  Both parts are sums of FP32 products:
 // the head on the matrix cores, the tail exactly in 64-bit fixed point (so its sum does not
 // depend on the order in which threads add); the squared distance is
 // |a|^2 + |b|^2 - 2 (a_h.b_h + a_t.b_t) as in the other FP32 kernel sums.
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(HT_BLOCK) void kernel_sum_ht_kernel(HtArgs A) {
             }
         }
     }
-    __syncthreads();   // hash and entries complete
+    __syncthreads();   // table and entries complete
 
     uint2* desc = reinterpret_cast<uint2*>(smem + L::desc) + HT_HITS * wid;
     unsigned long long* marks = reinterpret_cast<unsigned long long*>(smem + L::marks) + HT_HITS * wid;
