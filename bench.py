@@ -94,7 +94,8 @@ def recon_summary(results, data):
     ms = sum(r.ms_ksum for r in results)
     pairs = sum(r.recon_pairs for r in results)
     last = results[-1]
-    kern = ("kernel_sum_mfma_kernel" if last.ksum_mfma == 1
+    kern = ("kernel_sum_dense_kernel" if last.ksum_mfma == 1 and data.d <= 128
+            else "kernel_sum_mfma_kernel" if last.ksum_mfma == 1
             else "kernel_sum_ht_kernel" if last.ksum_mfma == 2
             else "kernel_sum_bits_kernel" if data.layout == "csr" and last.pattern_only and data.d <= 1024
             else "kernel_sum_slot_kernel" if data.layout == "csr" and data.d > 12288 else "kernel_sum_kernel")
