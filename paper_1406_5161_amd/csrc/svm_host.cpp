@@ -307,6 +307,7 @@ struct Solver {
     StepLds plan_lds{};
     int nseg_max = 0;
     long long nnz_seg_max = 0;
+    int loop_grid = 0;      // workgroups of the loop where that is not G, the grid that seg, cnt and act are for
     unsigned long long rows_streamed = 0, nnz_streamed = 0, rows_read = 0, cache_values = 0;
     void* kcache = nullptr;          // kernel-row cache (NULL: off)
     unsigned long long* ktags = nullptr;
@@ -1141,7 +1142,7 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
             S.ms_step += ms;
             S.rows_streamed += rows;
             S.rows_read += rows;
-            S.G = G;
+            S.loop_grid = G;      // (S.G stays: the selection below goes by its segments)
             ++S.n_launch;
             if ((rc = S.read_ctl())) return rc;
             if (S.h.exit_reason == EXIT_ABORT) return SVM_EABORT;
@@ -1195,7 +1196,7 @@ int finish(Solver& S, int status, int n_recon, svm_result_t* out) {
         out->shrink_passes = S.h.shrink_passes;
         out->shrunk_total = S.h.shrunk_total;
         out->n_launches = S.n_launch;
-        out->grid_blocks = S.G;
+        out->grid_blocks = S.loop_grid ? S.loop_grid : S.G;
         out->ms_total = now_ms() - t_start;
         out->ms_step = S.ms_step;
         out->ms_recon = S.ms_recon;
