@@ -1093,8 +1093,7 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
             std::vector<RegArgs> ra;
             for (int p = 0; p < k; ++p) {
                 if (!((running >> p) & 1)) continue;
-                ra.push_back(sv[p]->reg_args(2.0 * params[p].eps, 0));
-                HIP_TRY(hipMemsetAsync(ra.back().rec, 0, sizeof(unsigned long long) * 2 * 8 * G, s));
+                ra.push_back(sv[p]->reg_args(2.0 * params[p].eps, 0));   // (records cleared by prepare)
             }
             HIP_TRY(hipEventRecord(e0, s));
             HIP_TRY(launch_reg(ra.data(), (int)ra.size(), lay, kprec == SVM_KERNEL_FP64, sv[0]->reg_w4, sv[0]->reg_r,
