@@ -1102,11 +1102,15 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& shm, unsigned 
                 }
             };
             using std::integral_constant;
-            // as many rows at a time as the list has for a lane group: rows beyond its end cost what rows do
+            // as many rows at a time as the list has for a lane group: rows beyond its end cost what rows do.
+            // (Bitset rows two at most: four take the serving kernel from 248 registers to 254, which the
+            // hardware rounds to 256, all that two waves a SIMD have.  Elementwise kernels of the caller then
+            // run on the free compute units alone, where grids of many workgroups wait for the loop to stop:
+            // 0.1 ms became 2 s.  300-bit rows, n = 8000, four members: 5.67 ms against 5.75 with four.)
             if (!rres) stream(integral_constant<int, 4>{}, integral_constant<bool, false>{});
             else if (nact <= NG) stream(integral_constant<int, 1>{}, integral_constant<bool, true>{});
             else if (nact <= 2 * NG) stream(integral_constant<int, 2>{}, integral_constant<bool, true>{});
-            else stream(integral_constant<int, 4>{}, integral_constant<bool, true>{});
+            else stream(integral_constant<int, bits ? 2 : 4>{}, integral_constant<bool, true>{});
             if (do_shrink) {
                 // rows the rule removed carry the shrunk bit: one stable in-place compaction of
                 // the list after the pass (each chunk is read before its first barrier and
