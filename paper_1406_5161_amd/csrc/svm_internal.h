@@ -231,8 +231,12 @@ struct ValPart {
     int32_t flags, n_pos, n_neg, max_row_nnz, nnz;
 };
 constexpr int VAL_BLOCKS_MAX = 256;
-// workgroups of the validation of n rows (a part each); their parts take at most n / 2 + 20 bytes
-inline int val_blocks(int n) { return n >= 64 * VAL_BLOCKS_MAX ? VAL_BLOCKS_MAX : (n + 63) / 64; }
+constexpr int VAL_SMALL = 8192;   // rows up to which its workgroups have 256 threads, beyond 1024
+// workgroups of the validation of n rows (a part each); their parts take at most n + 20 bytes
+inline int val_blocks(int n) {
+    const int rows = n <= VAL_SMALL ? 32 : 64;
+    return n >= rows * VAL_BLOCKS_MAX ? VAL_BLOCKS_MAX : (n + rows - 1) / rows;
+}
 hipError_t launch_validate(int n, int d, int lay, const float* x, int64_t ldx, int feature_major,
                            const int32_t* rp, const int32_t* col, const float* val, const int8_t* y, ValPart* part,
                            hipStream_t s);

@@ -29,60 +29,69 @@ int device_cu_count() {
 // strictly increasing columns in [0, d); the longest row and whether a value differs from 1.0.  A
 // workgroup checks a contiguous share of the rows (dense rows element by element, CSR rows by 16
 // lanes each, so the loads coalesce) and stores one part; the host adds the parts.  Bound by the
-// read of the samples.  Atomic counters in one place, as here before, cost about 250 ns per wave
-// that adds to them: 3.86 ms for 500,000 x 28 dense rows (a capped solve of them 78.4 ms, now
-// 74.3), 0.79 of the 2.16 ms of classifying 10,000 queries with 100,000 such rows (now 1.32).
-constexpr int VAL_BLOCK = 1024;
-__global__ __launch_bounds__(VAL_BLOCK) void validate_kernel(int n, int d, int lay, const float* __restrict__ x,
-                                                             int64_t ldx, int feature_major,
-                                                             const int32_t* __restrict__ rp,
-                                                             const int32_t* __restrict__ col,
-                                                             const float* __restrict__ val,
-                                                             const int8_t* __restrict__ y, ValPart* part) {
-    __shared__ ValPart s_p[VAL_BLOCK / 64];
+// read of the samples.  Atomic counters in one place cost about 250 ns per wave that adds to them:
+// 3.86 ms for 500,000 x 28 dense rows.
+// One instance per form of the rows (VAL_*_ROWS), so that each takes at most 16 registers, which is what
+// a serving loop leaves free on its compute units: workgroups of 256 threads then run beside it wherever
+// the hardware places them, where a grid of more workgroups than the eight free units would wait for the
+// loop to stop (2 s, and as long as it is busy).
+enum : int { VAL_CSR_ROWS, VAL_FEATURE_MAJOR, VAL_PACKED_ROWS, VAL_STRIDED_ROWS };
+template <int BLOCK, int ROWS>
+__global__ __launch_bounds__(BLOCK) void validate_kernel(int n, int d, const float* __restrict__ x, int64_t ldx,
+                                                         const int32_t* __restrict__ rp,
+                                                         const int32_t* __restrict__ col,
+                                                         const float* __restrict__ val,
+                                                         const int8_t* __restrict__ y, ValPart* part) {
+    __shared__ ValPart s_p[BLOCK / 64];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int r0 = (int)((long long)n * blockIdx.x / gridDim.x), r1 = (int)((long long)n * (blockIdx.x + 1) / gridDim.x);
-    int flags = 0, npos = 0, nneg = 0, maxn = 0;
-    if (y)
-        for (int i = r0 + tid; i < r1; i += VAL_BLOCK) {
-            const int8_t v = y[i];
-            npos += v == 1;
-            nneg += v == -1;
-            if (v != 1 && v != -1) flags |= VAL_MALFORMED;
-        }
-    if (lay == SVM_CSR) {
+    int flags = 0;
+    if constexpr (ROWS == VAL_CSR_ROWS) {
         const int nnz = rp[n];
-        for (int i = r0 + (tid >> 4); i < r1; i += VAL_BLOCK / 16) {
-            const int p0 = rp[i], p1 = rp[i + 1];
+        for (int i = r0 + (tid >> 4); i < r1; i += BLOCK / 16) {
+            int p = rp[i];
+            const int p1 = rp[i + 1];
             // (a row beyond the nonzeros means that a later pointer falls)
-            if (p1 < p0 || p0 < 0 || p1 > nnz || (i == 0 && p0 != 0)) {
+            const bool bad = p1 < p || p < 0 || p1 > nnz || (i == 0 && p != 0);
+            if (bad) {
                 flags |= VAL_MALFORMED;
                 continue;
             }
-            maxn = max(maxn, p1 - p0);
-            for (int p = p0 + (tid & 15); p < p1; p += 16) {
-                const int c = col[p], cp = p > p0 ? col[p - 1] : -1;
+            const int first = p;
+            for (p += tid & 15; p < p1; p += 16) {
+                const int cp = p > first ? col[p - 1] : -1, c = col[p];
                 const float v = val[p];
                 if (c < 0 || c >= d || c <= cp) flags |= VAL_MALFORMED;
                 if (!isfinite(v)) flags |= VAL_NONFINITE;
                 if (v != 1.0f) flags |= VAL_NOT_ONES;
             }
         }
-    } else if (feature_major) {
+    } else if constexpr (ROWS == VAL_FEATURE_MAJOR) {
         for (int k = 0; k < d; ++k)
-            for (int i = r0 + tid; i < r1; i += VAL_BLOCK)
+            for (int i = r0 + tid; i < r1; i += BLOCK)
                 if (!isfinite(x[(size_t)k * ldx + i])) flags |= VAL_NONFINITE;
-    } else if (ldx == d) {
+    } else if constexpr (ROWS == VAL_PACKED_ROWS) {
         const float* xb = x + (size_t)r0 * d;
         const size_t m = (size_t)(r1 - r0) * d;
 #pragma unroll 4
-        for (size_t e = tid; e < m; e += VAL_BLOCK)
+        for (size_t e = tid; e < m; e += BLOCK)
             if (!isfinite(xb[e])) flags |= VAL_NONFINITE;
     } else {
-        for (int i = r0 + wid; i < r1; i += VAL_BLOCK / 64)
+        for (int i = r0 + wid; i < r1; i += BLOCK / 64)
             for (int k = lane; k < d; k += 64)
                 if (!isfinite(x[(size_t)i * ldx + k])) flags |= VAL_NONFINITE;
     }
+    // (labels and row lengths in loops of their own: their sums would take registers in the one above)
+    int npos = 0, nneg = 0, maxn = 0;
+    if constexpr (ROWS == VAL_CSR_ROWS)
+        for (int i = r0 + tid; i < r1; i += BLOCK) maxn = max(maxn, rp[i + 1] - rp[i]);
+    if (y)
+        for (int i = r0 + tid; i < r1; i += BLOCK) {
+            const int8_t v = y[i];
+            npos += v == 1;
+            nneg += v == -1;
+            if (v != 1 && v != -1) flags |= VAL_MALFORMED;
+        }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         flags |= __shfl_xor(flags, off);
@@ -90,11 +99,11 @@ __global__ __launch_bounds__(VAL_BLOCK) void validate_kernel(int n, int d, int l
         nneg += __shfl_xor(nneg, off);
         maxn = max(maxn, __shfl_xor(maxn, off));
     }
-    if (lane == 0) s_p[wid] = ValPart{flags, npos, nneg, maxn, lay == SVM_CSR ? rp[n] : 0};
+    if (lane == 0) s_p[wid] = ValPart{flags, npos, nneg, maxn, ROWS == VAL_CSR_ROWS ? rp[n] : 0};
     __syncthreads();
     if (tid == 0) {
         ValPart t = s_p[0];
-        for (int w = 1; w < VAL_BLOCK / 64; ++w) {
+        for (int w = 1; w < BLOCK / 64; ++w) {
             t.flags |= s_p[w].flags;
             t.n_pos += s_p[w].n_pos;
             t.n_neg += s_p[w].n_neg;
@@ -104,10 +113,21 @@ __global__ __launch_bounds__(VAL_BLOCK) void validate_kernel(int n, int d, int l
     }
 }
 
+template <int ROWS>
+static void validate_rows(int n, int d, const float* x, int64_t ldx, const int32_t* rp, const int32_t* col,
+                          const float* val, const int8_t* y, ValPart* part, hipStream_t s) {
+    const int nb = val_blocks(n);
+    if (n <= VAL_SMALL) validate_kernel<256, ROWS><<<nb, 256, 0, s>>>(n, d, x, ldx, rp, col, val, y, part);
+    else validate_kernel<1024, ROWS><<<nb, 1024, 0, s>>>(n, d, x, ldx, rp, col, val, y, part);
+}
+
 hipError_t launch_validate(int n, int d, int lay, const float* x, int64_t ldx, int feature_major, const int32_t* rp,
                            const int32_t* col, const float* val, const int8_t* y, ValPart* part, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    validate_kernel<<<val_blocks(n), VAL_BLOCK, 0, s>>>(n, d, lay, x, ldx, feature_major, rp, col, val, y, part);
+    if (lay == SVM_CSR) validate_rows<VAL_CSR_ROWS>(n, d, x, ldx, rp, col, val, y, part, s);
+    else if (feature_major) validate_rows<VAL_FEATURE_MAJOR>(n, d, x, ldx, rp, col, val, y, part, s);
+    else if (ldx == d) validate_rows<VAL_PACKED_ROWS>(n, d, x, ldx, rp, col, val, y, part, s);
+    else validate_rows<VAL_STRIDED_ROWS>(n, d, x, ldx, rp, col, val, y, part, s);
     return hipGetLastError();
 }
 
