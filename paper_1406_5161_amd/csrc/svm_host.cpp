@@ -43,7 +43,7 @@ TraceCfg& trace_cfg() {
     return t;
 }
 int* last_step_info() {
-    static thread_local int v[5] = {0, 0, 0, 0, 0};   // mode, grid, lanes per row, layout, values all 1.0
+    static thread_local int v[6] = {};   // mode, grid, lanes per row, layout, values all 1.0, rows in registers
     return v;
 }
 unsigned long long*& prof_cfg() {
@@ -787,15 +787,25 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
                        : (q->flags & SVM_FLAG_NO_LDS_PAYLOAD) ? STEP_LDS_STATE : STEP_LDS_ALL;
     const int cus = std::max(1, device_cu_count());
     int G = q->grid_blocks;
-    const TuneClass tclass{TUNE_GRID, S.lay, q->kernel_precision, S.pattern_only, q->shrink_mode != SVM_SHRINK_NONE,
-                           p->n, p->d};
-    if (!G) G = tuned_shape(tclass);   // measured by svm_autotune for this class
+    // the shape that svm_autotune measured for this class on that loop, where the caller asks for none
+    auto tuned = [&](int loop) -> int {
+        if (q->grid_blocks) return 0;
+        return tuned_shape(TuneClass{TUNE_GRID, S.lay, q->kernel_precision, S.pattern_only,
+                                     q->shrink_mode != SVM_SHRINK_NONE, p->n, p->d, loop});
+    };
     // dense and bitset rows that fit the register file stay there (svm_regloop.h)
     if ((S.lay == LAY_DENSE || S.lay == LAY_BITS) && max_mode == STEP_LDS_ALL &&
         (S.plan.cache_rows == 0 || S.lay == LAY_BITS)) {
         const bool fp64 = q->kernel_precision == SVM_KERNEL_FP64;
         const int w4 = reg_width(S.lay, S.lay == LAY_BITS ? bits_wpr(p->d) : S.dpad);
-        const int g = std::min(G ? G : reg_grid_rule(fp64, w4, p->n, cus), p->n);
+        int g = G;
+        if (!g && (g = tuned(1))) {
+            // (a class spans sizes up to two apart: no fewer workgroups than hold this one's rows)
+            const int most = REG_BLOCK * reg_rows_max(fp64, w4);
+            g = std::max(g, (p->n + most - 1) / most);
+        }
+        if (!g) g = reg_grid_rule(fp64, w4, p->n, cus);
+        g = std::min(g, p->n);
         const int r = w4 ? reg_rows(fp64, w4, (p->n + g - 1) / g) : 0;
         if (r && g <= REG_GRID_MAX && reg_max_blocks(S.lay, fp64, w4, r) >= g) {
             S.reg_w4 = w4;
@@ -803,6 +813,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
             G = g;
         }
     }
+    if (!G) G = tuned(0);
     if (!G) G = step_grid_rule(S.lay, p->n, cus);
     G = std::min(G, p->n);
     const double avg_nnz = p->layout == SVM_CSR ? (double)hrp[p->n] / (double)p->n : 0.0;
@@ -847,7 +858,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
         }
     };
     if (!S.reg_r) {
-        const bool chosen = q->grid_blocks || tuned_shape(tclass);
+        const bool chosen = q->grid_blocks || tuned(0);
         if ((rc = shape(G, max_mode, 0))) return rc;
         if (!chosen && p->layout == SVM_CSR && S.lay != LAY_BITS) {
             // The residency and lanes per row set the order in which a row's products are added, so
@@ -889,6 +900,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
     last_step_info()[2] = S.lpr;
     last_step_info()[3] = S.lay;
     last_step_info()[4] = S.pattern_only ? 1 : 0;
+    last_step_info()[5] = S.reg_r ? 1 : 0;
     S.nseg_max = (p->n + G - 1) / G;
     S.nnz_seg_max = 0;
     if (!hrp.empty())
@@ -1608,7 +1620,7 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
         if (std::find(cand.begin(), cand.end(), v) == cand.end()) cand.push_back(v);
     };
     svm_result_t r{};
-    int lay = 0, pattern = 0;
+    int lay = 0, pattern = 0, loop = 0;
     if (target == SVM_TUNE_GRID) {
         // around the rule of the loop that the problem takes
         const int cus = std::max(1, device_cu_count());
@@ -1668,7 +1680,11 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
         }
         if (out) { out->shape[c] = used; out->us_per_iter[c] = us; }
         shape_us.push_back({used, us});
-        if (!chosen || us < best) { best = us; chosen = used; }
+        if (!chosen || us < best) {
+            best = us;
+            chosen = used;
+            if (target == SVM_TUNE_GRID) loop = last_step_info()[5];
+        }
     }
     cleanup();
     if (target == SVM_TUNE_TEAM) {
@@ -1682,7 +1698,7 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
             }
     }
     const TuneClass tc{target == SVM_TUNE_GRID ? TUNE_GRID : TUNE_TEAM, lay, params->kernel_precision, pattern != 0,
-                       params->shrink_mode != SVM_SHRINK_NONE, n, prob->d};
+                       params->shrink_mode != SVM_SHRINK_NONE, n, prob->d, loop};
     set_tuned_shape(tc, chosen);
     if (out) {
         out->n_candidates = nc;

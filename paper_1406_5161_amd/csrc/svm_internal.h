@@ -382,6 +382,7 @@ struct TuneClass {
     int lay, kprec;
     bool pattern, shrink;
     long long n, d;
+    int loop = 0;             // TUNE_GRID: 1 the loop with its rows in registers, 0 svm_step.hip's
 };
 int tuned_shape(const TuneClass& c);   // 0: not tuned
 void set_tuned_shape(const TuneClass& c, int shape);

@@ -1,6 +1,6 @@
 // svm_tune.cpp -- the shape autotuner of libsvmhip.so: launch shapes measured on the device
-// per problem class and kept for the life of the process.  A class is the row layout, the
-// kernel-value precision, whether values are all 1.0, whether shrinking is on, and the sizes
+// per problem class and kept for the life of the process.  A class is the loop that runs it (rows in
+// registers or not), the row layout, the kernel-value precision, whether values are all 1.0, whether shrinking is on, and the sizes
 // n and d rounded up to powers of two.  The shapes tuned here (the SMO loop's workgroup
 // count, a batched problem's team size) only change how work is spread: the selection is
 // exact and f is updated row by row, so results are the same for every shape.
@@ -22,7 +22,7 @@ int log2_ceil(long long v) {
     return b;
 }
 
-using Key = std::tuple<int, int, int, int, int, int, int>;
+using Key = std::tuple<int, int, int, int, int, int, int, int>;
 
 struct TuneTable {
     std::mutex m;
@@ -34,7 +34,7 @@ TuneTable& table() {
 }
 
 Key key_of(const TuneClass& c) {
-    return Key(c.target, c.lay, c.kprec, c.pattern ? 1 : 0, c.shrink ? 1 : 0, log2_ceil(c.n), log2_ceil(c.d));
+    return Key(c.target, c.loop, c.lay, c.kprec, c.pattern ? 1 : 0, c.shrink ? 1 : 0, log2_ceil(c.n), log2_ceil(c.d));
 }
 
 }  // namespace
