@@ -318,6 +318,7 @@ struct Solver {
     unsigned long long* ktags = nullptr;
     int cache_rows = 0;
     uint32_t epoch = 0;
+    int trial = -1;                  // svm_autotune's trials: as if this shape were the tuned one (0: none)
     int reg_w4 = 0, reg_r = 0;       // the loop with its rows in registers: its instance (0: svm_step.hip's)
     int kfull = 0;                   // the cache holds the whole kernel matrix
     double ms_kmatrix = 0;
@@ -790,6 +791,7 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
     // the shape that svm_autotune measured for this class on that loop, where the caller asks for none
     auto tuned = [&](int loop) -> int {
         if (q->grid_blocks) return 0;
+        if (S.trial >= 0) return S.trial;
         return tuned_shape(TuneClass{TUNE_GRID, S.lay, q->kernel_precision, S.pattern_only,
                                      q->shrink_mode != SVM_SHRINK_NONE, p->n, p->d, loop});
     };
@@ -813,7 +815,11 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
             G = g;
         }
     }
-    if (!G) G = tuned(0);
+    // CSR rows of svm_step.hip: the residency and lanes per row set the order in which a row's products
+    // are added, so they stay those of the rule's grid whatever grid they are spread over
+    const bool csr_rows = p->layout == SVM_CSR && S.lay != LAY_BITS;
+    const int tuned_step = S.reg_r ? 0 : tuned(0);
+    if (!G && !csr_rows) G = tuned_step;
     if (!G) G = step_grid_rule(S.lay, p->n, cus);
     G = std::min(G, p->n);
     const double avg_nnz = p->layout == SVM_CSR ? (double)hrp[p->n] / (double)p->n : 0.0;
@@ -858,23 +864,26 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
         }
     };
     if (!S.reg_r) {
-        const bool chosen = q->grid_blocks || tuned(0);
         if ((rc = shape(G, max_mode, 0))) return rc;
-        if (!chosen && p->layout == SVM_CSR && S.lay != LAY_BITS) {
-            // The residency and lanes per row set the order in which a row's products are added, so
-            // they stay those of that grid; the rows then spread over as many workgroups as hold
-            // them in one pass (1024 / lanes rows each).  Text-like n = 20,000, eight lanes, row
-            // cache: 9.4 / 9.8 / 10.4 / 13.5 us per iteration at G = 192 / 128 / 64 / 29 (the grid of
-            // 700 rows each); two passes or fewer on one workgroup need no exchange.
+        if (!q->grid_blocks && csr_rows) {
+            // The rows spread over as many workgroups as hold them in one pass (1024 / lanes rows each), or
+            // the tuned number.  Text-like n = 20,000, eight lanes, row cache: 9.4 / 9.8 / 10.4 / 13.5 us per
+            // iteration at G = 192 / 128 / 64 / 29 (the grid of 700 rows each); two passes or fewer on one
+            // workgroup need no exchange.
             const int per = STEP_BLOCK / S.lpr;
-            int g2 = std::max(1, std::min(cus, (p->n + per - 1) / per));
-            if (g2 > G && !(G == 1 && p->n <= 2 * per)) {
+            int g2 = tuned_step;
+            if (!g2) {
+                g2 = std::max(1, std::min(cus, (p->n + per - 1) / per));
+                if (g2 < G || (G == 1 && p->n <= 2 * per)) g2 = G;
+            }
+            g2 = std::min(g2, p->n);
+            if (g2 != G) {
                 const StepLds was = plan;
-                const int lpr = S.lpr;
+                const int lpr = S.lpr, least = tuned_step ? 1 : G + 1;
                 // (state in LDS or not makes no difference to the order)
                 const bool rows_lds = was.mode == STEP_LDS_ALL;
                 if (shape(g2, rows_lds ? max_mode : std::min<int>(max_mode, STEP_LDS_STATE), lpr) == SVM_OK &&
-                    (plan.mode == STEP_LDS_ALL) == rows_lds && g2 > G) {
+                    (plan.mode == STEP_LDS_ALL) == rows_lds && g2 >= least) {
                     G = g2;
                 } else {
                     plan = was;
@@ -933,8 +942,9 @@ int prepare(Solver& S, const svm_problem_t* p, const svm_params_t* q, double* al
 }
 
 int train_impl(const svm_problem_t* p, const svm_params_t* q, double* alpha, double* f_out, svm_result_t* out,
-               void* workspace, size_t ws_bytes, hipStream_t s) {
+               void* workspace, size_t ws_bytes, hipStream_t s, int trial = -1) {
     Solver S{};
+    S.trial = trial;
     int rc = prepare(S, p, q, alpha, f_out, workspace, ws_bytes, s);
     if (rc) return rc;
     const double eps = q->eps;
@@ -1620,24 +1630,19 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
         if (std::find(cand.begin(), cand.end(), v) == cand.end()) cand.push_back(v);
     };
     svm_result_t r{};
-    int lay = 0, pattern = 0, loop = 0;
+    int lay = 0, pattern = 0, loop = 0, rule = 0;
+    size_t ws_bytes = 0;
     if (target == SVM_TUNE_GRID) {
-        // around the rule of the loop that the problem takes
+        // around the grid that a solve takes by itself: a first trial validates the problem and tells it
         const int cus = std::max(1, device_cu_count());
-        bool pat = false;
-        if (prob->layout == SVM_CSR && (rc = csr_pattern_only(prob, reinterpret_cast<int32_t*>(f), s, &pat))) {
-            cleanup();
-            return rc;
-        }
-        const int rl = prob->layout != SVM_CSR ? LAY_DENSE : pat && prob->d <= BITS_MAX_D ? LAY_BITS : LAY_CSR_TABLE;
-        const int w4 = rl == LAY_CSR_TABLE ? 0 : reg_width(rl, rl == LAY_BITS ? bits_wpr(prob->d) : dpad_of(prob->d));
-        const bool fp64 = q.kernel_precision == SVM_KERNEL_FP64;
-        const int g0 = w4 ? reg_grid_rule(fp64, w4, n, cus) : step_grid_rule(rl, n, cus);
-        for (int v : {g0 / 2, (3 * g0) / 4, g0, std::min(cus, (5 * g0) / 4), std::min(cus, (3 * g0) / 2)})
+        q.grid_blocks = 0;
+        ws_bytes = svm_train_workspace_size(prob, &q);
+        if (!ws_bytes || hipMalloc(&ws, ws_bytes) != hipSuccess) { cleanup(); return SVM_ENOMEM; }
+        rc = train_impl(prob, &q, alpha, f, &r, ws, ws_bytes, s, 0);
+        if (rc < 0) { cleanup(); return rc; }
+        rule = r.grid_blocks;
+        for (int v : {rule, rule / 2, (3 * rule) / 4, std::min(cus, (5 * rule) / 4), std::min(cus, (3 * rule) / 2)})
             if (v <= n) add(v);
-        q.grid_blocks = cand.back();
-        const size_t bytes = svm_train_workspace_size(prob, &q);
-        if (!bytes || hipMalloc(&ws, bytes) != hipSuccess) { cleanup(); return SVM_ENOMEM; }
     } else {
         // the team rule needs the nonzero count and whether every value is 1.0: one trial
         // solve on the automatic team tells the layout
@@ -1664,11 +1669,12 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
     int chosen = 0;
     std::vector<std::pair<int, double>> shape_us;
     const int nc = std::min<int>((int)cand.size(), 8);
+    int measured = 0;
     for (int c = 0; c < nc; ++c) {
-        q.grid_blocks = cand[c];
+        if (target == SVM_TUNE_TEAM) q.grid_blocks = cand[c];
         double us = 0.0;
         for (int rep = 0; rep < 2; ++rep) {   // the second run is timed
-            if (target == SVM_TUNE_GRID) rc = train_impl(prob, &q, alpha, f, &r, ws, svm_train_workspace_size(prob, &q), s);
+            if (target == SVM_TUNE_GRID) rc = train_impl(prob, &q, alpha, f, &r, ws, ws_bytes, s, cand[c]);
             else rc = svm_train_batch(1, prob, &q, &alpha, &f, &r, stream);
             if (rc < 0) { cleanup(); return rc; }
             us = r.iterations > 0 ? r.ms_step * 1e3 / (double)r.iterations : 0.0;
@@ -1677,14 +1683,15 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
         if (target == SVM_TUNE_GRID) {
             lay = last_step_info()[3];
             pattern = last_step_info()[4];
+            loop = last_step_info()[5];
         }
-        if (out) { out->shape[c] = used; out->us_per_iter[c] = us; }
+        bool again = false;                   // a shape that does not fit is run as one that does
+        for (const auto& t : shape_us) again = again || t.first == used;
+        if (again) continue;
+        if (out) { out->shape[measured] = used; out->us_per_iter[measured] = us; }
+        ++measured;
         shape_us.push_back({used, us});
-        if (!chosen || us < best) {
-            best = us;
-            chosen = used;
-            if (target == SVM_TUNE_GRID) loop = last_step_info()[5];
-        }
+        if (!chosen || us < best) { best = us; chosen = used; }
     }
     cleanup();
     if (target == SVM_TUNE_TEAM) {
@@ -1699,9 +1706,10 @@ int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t 
     }
     const TuneClass tc{target == SVM_TUNE_GRID ? TUNE_GRID : TUNE_TEAM, lay, params->kernel_precision, pattern != 0,
                        params->shrink_mode != SVM_SHRINK_NONE, n, prob->d, loop};
-    set_tuned_shape(tc, chosen);
+    // (the grid that solves take by themselves needs no entry: another size of the class takes its own)
+    set_tuned_shape(tc, target == SVM_TUNE_GRID && chosen == rule ? 0 : chosen);
     if (out) {
-        out->n_candidates = nc;
+        out->n_candidates = measured;
         out->chosen = chosen;
     }
     return SVM_OK;

@@ -54,3 +54,36 @@ def test_the_other_loop_keeps_its_rule(S):
     assert rc == S.SVM_OK
     after, again = solve(S, dp, n, cached)
     assert again == info and equal(before, after)
+
+
+@pytest.mark.parametrize("kind", ["text", "values", "dense"])
+def test_tuned_grid_is_no_slower_than_the_one_taken_without(S, kind):
+    """The grid that a solve takes by itself is among the candidates, and the tuned solve gives its bits."""
+    r = np.random.default_rng(4)
+    n = 6000
+    if kind == "dense":
+        data = g.gen_blobs(n, 40, r)
+    else:
+        data = g.gen_text_like(n, 20000, 60, r) if kind == "text" else g.gen_sparse_binary(n, 300, 0.12, r)
+        data.val = (data.val * r.uniform(0.5, 1.5, len(data.val))).astype(np.float32)
+    par = S.make_params(2.0, 0.05 if kind == "dense" else 0.5, 1e-3, 0, 0, 0.0, 400, S.SVM_KERNEL_FP32)
+    dp = S.to_device(data)
+    before, info = solve(S, dp, n, par)
+    rc, tune = S.svm_autotune(dp, par, S.SVM_TUNE_GRID)
+    assert rc == S.SVM_OK
+    print(kind, info, tune, flush=True)
+    us = {c["shape"]: c["us_per_iter"] for c in tune["candidates"]}
+    assert len(us) == len(tune["candidates"]) and info[1] in us
+    assert us[tune["chosen"]] <= us[info[1]]
+    after, again = solve(S, dp, n, par)
+    assert again[1] == tune["chosen"] and again[2] == info[2]
+    assert equal(before, after)
+
+
+def test_malformed_rows_are_refused(S):
+    dp = S.to_device(g.gen_sparse_binary(500, 300, 0.12, np.random.default_rng(6)))
+    par = S.make_params(1.0, 0.01, 1e-3, 0, 0, 0.0, 50, S.SVM_KERNEL_FP32)
+    rp = dp.keep[0]
+    rp[200] = rp[201] + 1      # the next pointer falls
+    for target in (S.SVM_TUNE_GRID, S.SVM_TUNE_TEAM):
+        assert S.svm_autotune(dp, par, target)[0] == S.SVM_EINVAL
