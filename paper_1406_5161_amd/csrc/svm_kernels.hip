@@ -1001,6 +1001,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
     const int brow = tid >> 2, bsub = tid & 3;
     uint32_t hw[NW];
     double pc = 0.0;
+    int pad = 0;   // rows beyond the split count one bit: no distance 0, whose value is NaN where -gamma is -inf in FP32
     auto load = [&](int c0) {
         const int j = c0 + brow;
         const bool in = j < b1;
@@ -1010,6 +1011,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
             const int w = bsub + 4 * k;
             hw[k] = in && w < wpr ? row[w] : 0u;
         }
+        pad = in ? 0 : 1;
         pc = in ? A.coef[j] : 0.0;
     };
     auto store = [&](int buf) {
@@ -1027,7 +1029,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
         c = xor_add<1>(c);
         c = xor_add<2>(c);
         if (bsub == 0) {
-            counts(buf)[brow] = c;
+            counts(buf)[brow] = c + pad;
             coefs(buf)[brow] = pc;
         }
     };
