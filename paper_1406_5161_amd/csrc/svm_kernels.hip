@@ -936,8 +936,8 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_mfma_kernel(SumArgs A) {
 }
 
 // Binary rows as bitsets (LAY_BITS): the intersections |a & b| are products of 0/1 bytes on the matrix
-// cores (v_mfma_i32_16x16x64_i8, exact), the squared distance |a| + |b| - 2 |a & b| is a whole number of
-// at most 2 d, and the kernel value comes from a table over those, formed once per workgroup by the
+// cores (v_mfma_i32_16x16x64_i8, exact), the squared distance |a| + |b| - 2 |a & b| = |a ^ b| is a whole
+// number of at most d, and the kernel value comes from a table over those, formed once per workgroup by the
 // expression the other kernels use: no exponential per pair, in FP64 none of its 40 instructions either.
 // A workgroup (4 waves) takes 64 RT rows of A, whose bytes stay in registers (lane (row, g) holds bits
 // 64 s + 16 g .. of its row for step s; B alike, so the order of the columns does not matter), and sweeps
@@ -957,7 +957,9 @@ DEV i32x4 bits_to_bytes(uint32_t h) {
 }
 
 // dynamic LDS: the table, then two buffers of a chunk's bytes, bit counts and coefficients
-constexpr size_t mb_table_bytes(int d) { return ((size_t)(2 * d + 1) * sizeof(double) + 15) & ~(size_t)15; }
+// (distances 0 .. d; rows beyond the split have one bit and no column: up to d + 1)
+__host__ __device__ constexpr int mb_table_entries(int d) { return d + 2; }
+constexpr size_t mb_table_bytes(int d) { return ((size_t)mb_table_entries(d) * sizeof(double) + 15) & ~(size_t)15; }
 constexpr size_t mb_buffer_bytes(int NS) { return (size_t)NS * 4 * MB_CHUNK * 16 + MB_CHUNK * (sizeof(int) + sizeof(double)); }
 
 template <typename KT, int NS, int RT>
@@ -972,7 +974,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
     const int m16 = lane & 15, mk = lane >> 4;
     const int wpr = A.wpr;
     const KT gam = (KT)A.gamma;
-    for (int k = tid; k <= 2 * A.d; k += SUM_BLOCK) tab[k] = (double)kexp((KT)(-gam * (KT)k));
+    for (int k = tid; k < mb_table_entries(A.d); k += SUM_BLOCK) tab[k] = (double)kexp((KT)(-gam * (KT)k));
     const int r0 = blockIdx.x * 64 * RT + 16 * RT * wid;   // the wave's first row
     i32x4 ar[RT][NS];
     int na[RT][4];
