@@ -1103,14 +1103,15 @@ __device__ __attribute__((noinline)) void solve_team(BatchShared& shm, unsigned 
             };
             using std::integral_constant;
             // as many rows at a time as the list has for a lane group: rows beyond its end cost what rows do.
-            // (Bitset rows two at most: four take the serving kernel from 248 registers to 254, which the
-            // hardware rounds to 256, all that two waves a SIMD have.  Elementwise kernels of the caller then
-            // run on the free compute units alone, where grids of many workgroups wait for the loop to stop:
-            // 0.1 ms became 2 s.  300-bit rows, n = 8000, four members: 5.67 ms against 5.75 with four.)
-            if (!rres) stream(integral_constant<int, 4>{}, integral_constant<bool, false>{});
+            // (Bitset rows from memory two at a time: with four, the serving kernel takes 254 registers, which
+            // the hardware rounds to 256, all that two waves a SIMD have, and an elementwise kernel of the
+            // caller waits until the loop stops: 2 s for 0.1 ms.  Such rows belong to teams that do not hold
+            // them: 20,000 x 1000 bits on 8 members 12.8 ms against 14.1 with four, 100,000 x 1000 on 64 10.45
+            // against 10.27, 8000 x 300 on one 14.5 against 13.5.)
+            if (!rres) stream(integral_constant<int, bits ? 2 : 4>{}, integral_constant<bool, false>{});
             else if (nact <= NG) stream(integral_constant<int, 1>{}, integral_constant<bool, true>{});
             else if (nact <= 2 * NG) stream(integral_constant<int, 2>{}, integral_constant<bool, true>{});
-            else stream(integral_constant<int, bits ? 2 : 4>{}, integral_constant<bool, true>{});
+            else stream(integral_constant<int, 4>{}, integral_constant<bool, true>{});
             if (do_shrink) {
                 // rows the rule removed carry the shrunk bit: one stable in-place compaction of
                 // the list after the pass (each chunk is read before its first barrier and
