@@ -212,7 +212,7 @@ int ht_nsplit(int na, int rows, int nb) {
 // the last round of them ends first (a workgroup's start and end cost about two chunks).  Sums of at most
 // four chunks for each of eight workgroups take no more than eight: those run at once on the compute
 // units that a serving loop leaves free, where the rest of a larger grid would wait for the loop to stop
-// (2 s after its last work; 16 queries against 5000 samples of 20 columns: 62.4 us against 61.2 with 15 splits).
+// (2 s after its last work; 16 queries against 5000 samples of 20 columns: 61.1 us, 60.8 with 15 splits).
 int dense_nsplit(long long blocks, long long nb, int most) {
     const long long chunks = std::max<long long>(1, (nb + 63) / 64), slots = 4ll * std::max(1, device_cu_count());
     constexpr long long FREE = 8;

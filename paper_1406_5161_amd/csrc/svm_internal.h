@@ -232,9 +232,10 @@ struct ValPart {
 };
 constexpr int VAL_BLOCKS_MAX = 256;
 constexpr int VAL_SMALL = 8192;   // rows up to which its workgroups have 256 threads, beyond 1024
-// workgroups of the validation of n rows (a part each); their parts take at most n + 20 bytes
+// workgroups of the validation of n rows (a part each): a row for each group of 16 threads, if that
+// makes no more than VAL_BLOCKS_MAX; their parts take at most 2 n + 20 bytes
 inline int val_blocks(int n) {
-    const int rows = n <= VAL_SMALL ? 32 : 64;
+    const int rows = n <= 16 * VAL_BLOCKS_MAX ? 16 : n <= VAL_SMALL ? 32 : 64;
     return n >= rows * VAL_BLOCKS_MAX ? VAL_BLOCKS_MAX : (n + rows - 1) / rows;
 }
 hipError_t launch_validate(int n, int d, int lay, const float* x, int64_t ldx, int feature_major,

@@ -83,8 +83,8 @@ def test_calls_run_beside_the_loop():
         assert same and dt < 1.0, (name, dt, same)
 
 
-@pytest.mark.parametrize("n", [31, 32, 33, 8191, 8192, 8193])
-def test_validation_around_its_two_workgroup_sizes(n):
+@pytest.mark.parametrize("n", [16, 17, 4095, 4096, 4097, 8191, 8192, 8193])
+def test_validation_around_its_workgroup_sizes(n):
     from tests import test_gpu_validate as v
     for layout in ("rows", "strided", "features"):
         v.test_dense(n, layout)
