@@ -1,0 +1,28 @@
+"""The dense FP32 kernel sum (products on the matrix cores, norms from a pass of their own) against NumPy in
+64 bits, at the edges of its tiles, chunks and widths."""
+import numpy as np
+import pytest
+
+from paper_1406_5161_amd import datagen as g
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,nq,d", [(2, 1, 1), (63, 64, 4), (64, 63, 5), (65, 65, 20), (130, 17, 33), (500, 129, 48),
+                                    (1100, 15, 64), (300, 200, 65), (400, 70, 100), (1000, 300, 128), (5000, 3, 28)])
+def test_against_64_bits(n, nq, d):
+    from paper_1406_5161_amd import svmhip as S
+    r = np.random.default_rng([n, nq, d])
+    train, query = g.gen_blobs(n, d, r), g.gen_blobs(nq, d, r)
+    alpha = r.uniform(0.0, 1.0, n) * (r.random(n) < 0.8)
+    gamma, beta = 1.0 / d, 0.25
+    x, z = train.x.astype(np.float64), query.x.astype(np.float64)
+    x2, z2 = (x * x).sum(1), (z * z).sum(1)
+    d2 = np.maximum(z2[:, None] + x2[None, :] - 2.0 * (z @ x.T), 0.0)
+    k = np.exp(-gamma * d2)
+    got = S.decision_data(train, alpha, beta, gamma, query, kernel_precision=S.SVM_KERNEL_FP32)
+    # each of |a|^2, |b|^2 and 2 a.b is a sum of d FP32 products, then two additions: at most d + 3 roundings of
+    # at most |a|^2 + |b|^2 each way; |K / e^v - 1| <= (|v| + 1) 2^-21 for the exponential
+    err = gamma * (d + 3) * 2.0 ** -23 * (z2[:, None] + x2[None, :]) + (gamma * d2 + 1.0) * 2.0 ** -21
+    tol = (k * np.expm1(err)) @ alpha + 1e-13
+    assert np.all(np.abs(got - (k @ (alpha * train.y) - beta)) <= tol)
