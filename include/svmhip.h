@@ -145,8 +145,9 @@ typedef struct {
     int64_t nnz_streamed;     /* CSR: nonzeros of those rows (0 for dense) */
     int32_t pattern_only;     /* CSR values were all 1.0 and were not read */
     int32_t lanes_per_row;    /* CSR lanes per row used by the step */
-    int32_t ksum_mfma;        /* reconstruction sums on the matrix cores: 1 dense rows (FP32), 2 the dense head
-                                 of wide CSR rows (FP32), 0 none */
+    int32_t ksum_mfma;        /* reconstruction sums in FP32 products on the matrix cores: 1 dense rows, 2 the
+                                 dense head of wide CSR rows; 0 others (bitset rows' sums, exact integer
+                                 products on the matrix cores, are among them) */
     double ms_ksum;           /* time in the reconstruction / recompute kernel-sum launches (HIP events) */
     int64_t recon_pairs;      /* (row, support vector) pairs those launches evaluated */
     int32_t head_cols;        /* head columns of the wide-CSR kernel sums (0: not used) */
@@ -167,7 +168,10 @@ size_t svm_train_workspace_size(const svm_problem_t* prob, const svm_params_t* p
  * out: host struct.  workspace/ws_bytes: device buffer of at least
  * svm_train_workspace_size() bytes, or NULL/0 to let the library allocate and
  * free one itself.  The inputs are validated on the device first
- * (SVM_EINVAL / SVM_EONECLASS / SVM_ENONFINITE). */
+ * (SVM_EINVAL / SVM_EONECLASS / SVM_ENONFINITE).  The workgroups of a launch
+ * wait for each other: up to 160 s until all of them run (other work may hold
+ * the device, such as a serving loop started meanwhile), then up to 5 s an
+ * iteration; SVM_EABORT beyond that. */
 int svm_train(const svm_problem_t* prob, const svm_params_t* params, double* alpha, double* f,
               svm_result_t* out, void* workspace, size_t ws_bytes, void* stream);
 
@@ -176,9 +180,9 @@ int svm_train(const svm_problem_t* prob, const svm_params_t* params, double* alp
  * "Data Structure Organization").  Problems that fit the chip together with their rows in
  * registers run side by side in one launch, each on its own workgroups.  Otherwise each SMO
  * iteration (Alg. 2, eq:fup, eq:bminmax) advances every unconverged problem and reads each row
- * once for all of them, so the row bytes per problem-iteration fall about k-fold.  x: the shared samples (its y is not used); y[p]: the
- * labels of problem p (device, n bytes); params[p]: its C, gamma, eps, max_iter and flags,
- * with shrink_mode SVM_SHRINK_NONE and one kernel_precision for all (SVM_EUNSUPPORTED
+ * once for all of them, so the row bytes per problem-iteration fall about k-fold.  x: the shared
+ * samples (its y is not used); y[p]: the labels of problem p (device, n bytes); params[p]: its
+ * C, gamma, eps, max_iter and flags, with shrink_mode SVM_SHRINK_NONE and one kernel_precision for all (SVM_EUNSUPPORTED
  * otherwise); alpha[p] / f[p] (f may be NULL) and out[p] as in svm_train.  1 <= k <= 8; rows
  * dense, or CSR whose values are all 1.0 with d <= 1024 (kept as bitsets); SVM_EUNSUPPORTED
  * for other CSR.  Every problem's arithmetic is its svm_train run's (same trajectory, same
@@ -252,8 +256,12 @@ int svm_train_batch(int32_t k, const svm_problem_t* probs, const svm_params_t* p
  * the loop largest estimated work (n^2 x bytes per row) first, and only while
  * the loop is short of work, so a burst finishes longest-first; a problem
  * prepared more than 3 s ago goes ahead of newer ones, oldest first.  While
- * the loop runs it holds all but 8 compute units, so other device work of the
- * process (copies, kernels) runs on those 8.  FP32 kernel values only. */
+ * the loop runs it holds all but 8 compute units.  Copies, launches of at most
+ * 8 workgroups and elementwise kernels (workgroups of 256 threads, 16 vector
+ * registers) run beside it, and so do small svm_decision calls; any other
+ * launch waits until the loop stops, svm_train, svm_train_shared and
+ * svm_train_batch among them.  A stream that HIP maps onto the loop's hardware
+ * queue waits too (four queues, streams in turn).  FP32 kernel values only. */
 int svm_server_create(size_t hbm_budget, int32_t max_slots, void** server);
 /* Queue a problem (its arrays must stay valid until the ticket completes).
  * alpha: n doubles (device) that receive the solution.  Returns a ticket; a
@@ -289,10 +297,12 @@ typedef struct {
  * SVM_TUNE_GRID the fastest (the problem has the GPU to itself), for SVM_TUNE_TEAM the one with
  * the fewest workgroup-microseconds per iteration among those within 1.5x of the fastest time
  * per iteration (a team shares the launch with other problems, so its cost is workgroups held
- * times time, with a bound on how much slower one problem may get): a
- * class is the row layout, kernel precision, whether all CSR values are 1.0, whether
- * shrinking is on, and n and d rounded up to powers of two.  The shapes only spread the work
- * differently (the selection of eq:bminmax is exact and f is updated row by row), so results
+ * times time, with a bound on how much slower one problem may get).  The grid that svm_train
+ * takes by itself is among the first kind's shapes; where it is the fastest, nothing is kept.
+ * A class is the loop (rows in registers or not), the row layout, kernel precision, whether
+ * all CSR values are 1.0, whether shrinking is on, and n and d rounded up to powers of two; a
+ * problem whose rows need more workgroups than were kept takes as many as hold them.  The
+ * shapes only spread the work differently (the selection of eq:bminmax is exact and f is updated row by row), so results
  * do not depend on them.  Allocates trial buffers; alpha of the problem is not touched.
  * svm_autotune_reset forgets every class (the built-in rules apply again). */
 int svm_autotune(const svm_problem_t* prob, const svm_params_t* params, int32_t target, svm_tune_t* out,

@@ -1128,7 +1128,8 @@ int train_shared_impl(const svm_problem_t* x, int k, const int8_t* const* y, con
             HIP_TRY(hipEventRecord(e1, s));
             std::vector<unsigned long long> w(4 * (size_t)G);
             for (const RegArgs& r : ra) {
-                HIP_TRY(hipMemcpyAsync(w.data(), r.work, sizeof(unsigned long long) * w.size(), hipMemcpyDeviceToHost, s));
+                HIP_TRY(hipMemcpyAsync(w.data(), r.work, sizeof(unsigned long long) * w.size(), hipMemcpyDeviceToHost,
+                                       s));
                 HIP_TRY(hipStreamSynchronize(s));
                 for (int b = 0; b < G; ++b) rows += w[4 * b];
             }
@@ -1260,7 +1261,7 @@ int check_decision_args(const svm_problem_t* train, const svm_problem_t* queries
 }
 
 struct DecPlan {
-    size_t ctl, xt, xq, lz, cf, bc, ct, pt, tbits, qbits, htcnt, hthmap, htbits, thead, tnrm, ttcnt, qhead, qnrm, qtcnt,
+    size_t xt, xq, lz, cf, bc, ct, pt, tbits, qbits, htcnt, hthmap, htbits, thead, tnrm, ttcnt, qhead, qnrm, qtcnt,
         htmisc, bhead, bnrm, toff, tent, total;
 };
 
@@ -1273,7 +1274,7 @@ DecPlan make_dec_plan(const svm_problem_t* train, const svm_problem_t* queries, 
     DecPlan q{};
     size_t o = 0;
     auto take = [&](size_t b) { size_t at = o; o = align_up(o + b); return at; };
-    q.ctl = take(2 * CTL_BYTES);
+    take(16);   // the number of support vectors, where it goes in front of the packed rows
     q.xt = take(dense ? sizeof(float) * n * dpad : 0);
     q.xq = take(dense ? sizeof(float) * nq * dpad : 0);
     q.lz = take(sizeof(int32_t) * n);
@@ -1334,13 +1335,13 @@ int decision_impl(const svm_problem_t* train, const double* alpha, double beta, 
     // packed training rows go later, behind the number of support vectors, which needs nothing that
     // validation finds (a wrong label gives a wrong coefficient, not an access): one copy and one wait
     // for all three (16 queries, 2000 samples of 20 columns: 96 us a call with two waits and three
-    // copies, 59 with one of each and the list in one launch; 10,000 queries, 50,000 300-bit rows 261 and
-    // 227).  Where there is no such place they go
-    // where the coefficients (8 B a row) and the partial sums (128 B a query) go later.
+    // copies, 57 with one of each and the list in one launch; 10,000 queries, 50,000 300-bit rows 261 and
+    // 227).  Where there is no such place they go where the coefficients (8 B a row) and the partial sums
+    // (128 B a query) go later.
     const int vbt = val_blocks(n), vbq = val_blocks(nq);
     const size_t vbytes = sizeof(ValPart) * (size_t)(vbt + vbq);
     const bool bitrows = !dense && d <= BITS_MAX_D, htrows = !dense && !bitrows && ht_capable(train);
-    // (dense: the count stays at the end of the plan's control block, since packing reads it)
+    // (dense: the count stays in front of the packed rows, since packing reads it)
     unsigned char* place = dense ? ws + P.xt - 16 : bitrows ? ws + P.tbits : ws + P.thead;
     const size_t room = dense ? 16 + sizeof(float) * (size_t)n * dpad
                         : bitrows ? sizeof(uint32_t) * (size_t)n * bits_wpr(d)

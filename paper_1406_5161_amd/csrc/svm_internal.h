@@ -175,6 +175,9 @@ struct RegLaunch {
 };
 // Rows a thread can hold (1, 2 or 4) of W4 * 16 bytes each: at most 160 of the 256 registers, the rest
 // being the f, status and distances of the rows and the working set; FP64 distances take twice theirs.
+// All instances fit but one: four bitset rows of 769 to 1024 bits (128 registers of rows) spill 40.  It
+// runs only where two rows a thread are too few, and is the better loop there: 300,000 x 1000 bits 9.60 us
+// an iteration, 16.5 with the rows streamed (260,000 with two rows a thread 6.83).
 constexpr int reg_rows_max(bool fp64, int W4) { return W4 * 4 <= 40 && !fp64 ? 4 : W4 * 2 <= 40 ? 2 : 1; }
 // Row width (in 16-byte words) of the instance for rows of `stride` 4-byte words: the next that is
 // built; 0: none

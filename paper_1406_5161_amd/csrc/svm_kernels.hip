@@ -44,7 +44,8 @@ __global__ __launch_bounds__(BLOCK) void validate_kernel(int n, int d, const flo
                                                          const int8_t* __restrict__ y, ValPart* part) {
     __shared__ ValPart s_p[BLOCK / 64];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int r0 = (int)((long long)n * blockIdx.x / gridDim.x), r1 = (int)((long long)n * (blockIdx.x + 1) / gridDim.x);
+    const int r0 = (int)((long long)n * blockIdx.x / gridDim.x);
+    const int r1 = (int)((long long)n * (blockIdx.x + 1) / gridDim.x);
     int flags = 0;
     if constexpr (ROWS == VAL_CSR_ROWS) {
         const int nnz = rp[n];
@@ -154,7 +155,8 @@ hipError_t launch_pack_dense(int n, int d, int dpad, const float* x, int64_t ldx
                              hipStream_t s, const int32_t* list, const int32_t* count) {
     size_t tot = (size_t)n * dpad;
     if (!tot) return hipSuccess;
-    pack_dense_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(n, d, dpad, x, ldx, feature_major, out, list, count);
+    pack_dense_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(n, d, dpad, x, ldx, feature_major, out, list,
+                                                                    count);
     return hipGetLastError();
 }
 
@@ -964,7 +966,9 @@ DEV i32x4 bits_to_bytes(uint32_t h) {
 // (distances 0 .. d; rows beyond the split have one bit and no column: up to d + 1)
 __host__ __device__ constexpr int mb_table_entries(int d) { return d + 2; }
 constexpr size_t mb_table_bytes(int d) { return ((size_t)mb_table_entries(d) * sizeof(double) + 15) & ~(size_t)15; }
-constexpr size_t mb_buffer_bytes(int NS) { return (size_t)NS * 4 * MB_CHUNK * 16 + MB_CHUNK * (sizeof(int) + sizeof(double)); }
+constexpr size_t mb_buffer_bytes(int NS) {
+    return (size_t)NS * 4 * MB_CHUNK * 16 + MB_CHUNK * (sizeof(int) + sizeof(double));
+}
 
 template <typename KT, int NS, int RT>
 __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
@@ -1007,7 +1011,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_bits_kernel(SumArgs A) {
     const int brow = tid >> 2, bsub = tid & 3;
     uint32_t hw[NW];
     double pc = 0.0;
-    int pad = 0;   // rows beyond the split count one bit: no distance 0, whose value is NaN where -gamma is -inf in FP32
+    int pad = 0;   // rows beyond the split count one bit: distance 0 is NaN where gamma is infinite in FP32
     auto load = [&](int c0) {
         const int j = c0 + brow;
         const bool in = j < b1;

@@ -11,7 +11,7 @@
 //  * 512 threads (two waves per SIMD, 256 registers a lane), because the reductions and the merge
 //    are instruction-bound per wave and barriers cost by the wave;
 //  * every wave stages the pair for itself in its own LDS, so the stage needs no barrier: an
-//    iteration has two barriers (three beyond 8 workgroups) where svm_step.hip has five;
+//    iteration has two barriers (three beyond 8 workgroups) where svm_step.hip has four;
 //  * records of one 64-byte line (eight words of 48 payload bits and a 16-bit tag), read eight per
 //    load instruction: the exchange and its reductions alone take 2.9 / 3.4 / 4.3 us at 29 / 128 /
 //    256 workgroups, against 3.2 / 4.0 / 4.8 with the 128-byte records of svm_step.hip on 1024
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
     constexpr int NT = REG_BLOCK, NW = REG_NW, W = 4 * W4;
     typedef typename std::conditional<BITS, uint4, float4>::type V4;
     __shared__ double s_al[R * NT];                               // alpha of the segment's rows
-    __shared__ uint8_t s_lab[R * NT];                             // bit 0: label +1; bit 1: on the active list at launch
+    __shared__ uint8_t s_lab[R * NT];      // bit 0: label +1; bit 1: on the active list at launch
     __shared__ __align__(16) uint32_t s_pair[NW][2 * W];          // a wave's copy of the pair rows
     __shared__ unsigned long long s_rec[REG_GRID_MAX * 9];        // records (odd stride in 8-byte words)
     __shared__ double s_v[2 * NW], m_v[8], m_a[8];

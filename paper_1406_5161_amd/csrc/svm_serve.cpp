@@ -159,8 +159,8 @@ int team_size(const svm_problem_t* p, const Inspect& in, int workers, int reques
 // iteration costs about 3.5 us whatever the team (pair staging, reductions, the exchange: 1.5 us with two
 // members, 2.3 with 64) and `row` us per row a member holds; a solve takes of the order of n
 // iterations, but from a tenth of that to twice it, so each next member goes where n times the rows'
-// part is largest (24 problems of 1000 to 8000 samples, with the loop as it was then: 59.7 ms; by the
-// whole expected time, 63.9; without this rule, 147.1).  Measured for one problem alone, least team ->
+// part is largest; going by the whole expected time instead is 7 % slower.  24 problems of 1000 to 8000
+// samples, eight seeds: 48 to 78 ms a call, 59 on average, against 144 to 147 without this rule.  Measured for one problem alone, least team ->
 // 32 -> 64 members: 128 dense columns, n = 7308, 124 -> 42.2 -> 28.4 ms; 300-bit rows, n = 8000,
 // 71.8 -> 39.0 -> 41.6 ms.  Below 0.5 us of rows a member a larger team gains nothing, and a second
 // member pays for its exchange from 2 us of rows on (20 columns, n = 1000, 2.7 us: 2.77 ms alone, 2.48

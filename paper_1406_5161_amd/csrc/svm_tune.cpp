@@ -1,9 +1,10 @@
 // svm_tune.cpp -- the shape autotuner of libsvmhip.so: launch shapes measured on the device
-// per problem class and kept for the life of the process.  A class is the loop that runs it (rows in
-// registers or not), the row layout, the kernel-value precision, whether values are all 1.0, whether shrinking is on, and the sizes
-// n and d rounded up to powers of two.  The shapes tuned here (the SMO loop's workgroup
-// count, a batched problem's team size) only change how work is spread: the selection is
-// exact and f is updated row by row, so results are the same for every shape.
+// per problem class and kept for the life of the process.  A class is the loop that runs it (rows
+// in registers or not), the row layout, the kernel-value precision, whether values are all 1.0,
+// whether shrinking is on, and the sizes n and d rounded up to powers of two.  The shapes tuned
+// here (the SMO loop's workgroup count, a batched problem's team size) only change how work is
+// spread: the selection is exact and f is updated row by row, so results are the same for every
+// shape.
 #include <hip/hip_runtime.h>
 
 #include <map>
