@@ -730,7 +730,8 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_dense_kernel(SumArgs A) 
         if (tid < MD_CHUNK) {
             const int j = c0 + tid;
             const bool in = j < b1;
-            pn = in ? A.bnrm[A.blist ? A.blist[j] : j] : 0.f;
+            // (rows beyond the split: distance 0 would be NaN where gamma is infinite in FP32)
+            pn = in ? A.bnrm[A.blist ? A.blist[j] : j] : 1.f;
             pc = in ? A.coef[j] : 0.0;
         }
     };
@@ -909,7 +910,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void kernel_sum_mfma_kernel(SumArgs A) {
         if (tid < MF_T) {
             float sq = 0.f;
             for (int k = 0; k < dpad; ++k) sq = fmaf(bt[tid * S + k], bt[tid * S + k], sq);
-            s_nb[tid] = sq;
+            s_nb[tid] = tid < nc ? sq : 1.f;   // (rows beyond the end: as in kernel_sum_dense_kernel)
         }
         __syncthreads();
         const float* arow = at + (16 * wid + mrow) * S + mk;

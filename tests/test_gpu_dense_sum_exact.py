@@ -26,3 +26,19 @@ def test_against_64_bits(n, nq, d):
     err = gamma * (d + 3) * 2.0 ** -23 * (z2[:, None] + x2[None, :]) + (gamma * d2 + 1.0) * 2.0 ** -21
     tol = (k * np.expm1(err)) @ alpha + 1e-13
     assert np.all(np.abs(got - (k @ (alpha * train.y) - beta)) <= tol)
+
+
+@pytest.mark.parametrize("d", [3, 40, 128, 160])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 130])
+def test_gamma_beyond_fp32(n, d):
+    """gamma is finite and infinite as an FP32 number: every kernel value between different rows is 0, and rows
+    beyond a chunk's end add nothing, against a query of zeros too."""
+    from paper_1406_5161_amd import svmhip as S
+    x = np.zeros((n, d), np.float32)
+    x[:, 0] = 1.0 + np.arange(n)
+    y = np.where(np.arange(n) % 2, 1, -1).astype(np.int8)
+    train = g.SvmData("t", n, d, "dense", y, x=x)
+    query = g.SvmData("q", 3, d, "dense", np.ones(3, np.int8),
+                      x=np.stack([np.zeros(d), np.full(d, -1.0), np.zeros(d)]).astype(np.float32))
+    out = S.decision_data(train, np.full(n, 0.5), 0.25, 1e39, query, kernel_precision=S.SVM_KERNEL_FP32)
+    assert np.array_equal(out, np.full(3, -0.25))
