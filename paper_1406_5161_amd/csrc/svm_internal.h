@@ -135,11 +135,11 @@ StepLds plan_step_lds(int lay, int d, int dpad, int max_row_nnz, int nseg_max, l
 // ---- the loop with its rows in registers (svm_regloop.h): dense rows and bitset rows
 constexpr int REG_BLOCK = 512;        // threads per workgroup: 256 vector registers a lane
 constexpr int REG_GRID_MAX = 256;
-// The 16-bit tag of an iteration's selection records, 1 to 65,535: words cleared before a launch hold 0,
+// The 16-bit tag of an iteration's selection records, 1 to 32,768: words cleared before a launch hold 0,
 // and a launch may start at any iteration, so 0 is no tag.  A record's place is written every other
-// iteration, so an older tag there never equals the one waited for.
-__host__ __device__ constexpr unsigned rec_tag(int64_t iter) { return 1u + (unsigned)(iter % 65535); }
-__host__ __device__ constexpr unsigned rec_tag_next(unsigned tag) { return tag == 65535u ? 1u : tag + 1u; }
+// iteration, so an older tag there never equals the one waited for.  (Formed from the iteration in two
+// scalar instructions: a tag carried from one iteration to the next cost 0.5 % of a solve.)
+__host__ __device__ constexpr unsigned rec_tag(int64_t iter) { return ((unsigned)iter & 0x7fffu) + 1u; }
 // The test hooks' buffers, in device memory (out of the loop's scalar registers when not in use).
 struct RegDebug {
     int64_t trace_cap;

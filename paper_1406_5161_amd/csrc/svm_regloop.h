@@ -111,7 +111,6 @@ __global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
     int yu = iu >= 0 && A.y[iu] > 0 ? 1 : -1, yl = il >= 0 && A.y[il] > 0 ? 1 : -1;
     long long iter = ctl->iter, counter = ctl->counter, n_act_total = ctl->n_active;
     long long passes = ctl->shrink_passes, shrunk = ctl->shrunk_total;
-    unsigned tg = rec_tag(iter);
     int exit_reason = EXIT_NONE;
     unsigned long long work_rows = 0, work_nnz = 0;
     const bool dbg_on = A.dbg != nullptr && blk == 0 && tid == 0;
@@ -357,6 +356,7 @@ __global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
         int ncnt = nrows;
         if (G > 1) {
             const int par = (int)(iter & 1);
+            const unsigned tg = rec_tag(iter);
             unsigned long long* rec = A.rec + (size_t)par * G * 8;
             if (wid == 0 && lane < 8) {
                 const unsigned long long bub = (unsigned long long)__double_as_longlong(cbu);
@@ -503,7 +503,6 @@ __global__ __launch_bounds__(REG_BLOCK) void smo_reg_kernel(RegLaunch L) {
             if (counter < 1) counter = 1;
         }
         ++iter;
-        tg = rec_tag_next(tg);
         lap(4);
         if (prof_on) s_pt[5] += 1;
     }
